@@ -87,13 +87,16 @@ typedef enum pic_variant {
                                    activations split into bf16 high + low parts    */
     PIC_VARIANT_MFMA_F16X3 = 4  /* fp16 matrix cores (v_mfma_f32_16x16x32_f16) at
                                    binary32 accuracy: each fp32 weight and
-                                   activation is scaled by a power of two, split
-                                   into two fp16 parts, and every product is
-                                   formed from three partial products; requires
-                                   PIC_F32 weights.  Where a latent or bias is not
-                                   below 2^24 in magnitude (or not finite), or a
-                                   layer's largest weight is not in [2^-16, 2^24),
-                                   it runs the fp32 instructions instead           */
+                                   activation is split into two fp16 parts, and
+                                   every product is formed from three partial
+                                   products; levels, neurons and tiles are scaled
+                                   by powers of two, so that the parts hold what
+                                   magnitudes differ.  Requires PIC_F32 weights.
+                                   Pixels for which the parts may not hold enough,
+                                   and tiles or images with a latent, weight or
+                                   bias not below 2^24 in magnitude (or not
+                                   finite), run the fp32 instructions instead, at
+                                   about a third of MFMA_F32's speed               */
 } pic_variant;
 
 enum {

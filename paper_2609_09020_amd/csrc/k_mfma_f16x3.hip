@@ -42,8 +42,8 @@ bool mfma_f16x3_wide_supports(int L, int nl, const int32_t *widths)
     const int nb = mfma_f16x3::hidden_blocks(nl, widths);
     if (L < 1 || L > 12 || nl < 2 || nl > 4 || nb <= 4 || nb > 8)
         return false;
-    static_assert(mfma_f16x3::wide_fits<6, 2, 3> && mfma_f16x3::wide_fits<8, 1, 3> && mfma_f16x3::wide_fits<8, 2, 2> &&
-                      !mfma_f16x3::wide_fits<8, 2, 3>,
+    static_assert(mfma_f16x3::wide_fits<6, 2, 3, 2> && mfma_f16x3::wide_fits<8, 1, 3, 2> &&
+                      mfma_f16x3::wide_fits<8, 2, 2, 2> && !mfma_f16x3::wide_fits<8, 2, 3, 2>,
                   "the one shape the LDS does not hold");
     return !(nb > 6 && nl == 4 && L > 8);
 }

@@ -17,25 +17,50 @@
 // takes a third part of its weights, which leaves 4.4e-8, and the output
 // layer sums in two chains a lane where the fp32 family runs one.)
 //
-// Scaling, all by powers of two, so exact.  A layer's weights are scaled once
-// per workgroup by its largest magnitude, and a pixel's levels by the largest
-// of them (a column of the B operand: only that pixel's column of the product
-// scales).  The first layer's scales (weights below 2^5, levels below 2^6)
-// bound its scaled outputs by 13 2^11 < 2^15, so they are the hidden layer's
-// scaled inputs as they stand; a second hidden layer's inputs take a constant
-// factor 2^-22 (129 2^14 2^15 < 2^37).  Only the last hidden layer's outputs
-// are scaled back, after the output layer's sums.  A bias enters as one more
-// input: the weight b / rho against the activation rho, with the power of two
-// rho that gives the layer's largest bias a weight's magnitude; the pixel's
-// largest level is taken as at least what keeps those activations in range.
-// (The matrix cores keep subnormal fp16 inputs, so a part below 2^-14 loses
-// bits only below 2^-25: 2^-30 of the pixel's largest level, 2^-40 of a later
-// layer's bound.)
+// Scaling, all by powers of two, so exact.  fp16 keeps a value's 11 bits only
+// above 2^-14 and nothing below 2^-25, so every value must come near the top
+// of its range whatever the spread of the weights.  Each level k, neuron n and
+// tile gets a scale of its own (ReLU commutes with a positive factor):
 //
-// Range.  The scales fit while every layer's largest weight lies in [2^-16,
-// 2^24) or is zero, and every bias and latent is below 2^24 in magnitude.  A
-// tile outside that (NaN and infinities included) is evaluated by the fp32
-// matrix instructions instead.
+//   C_k: the power of two above level k's largest weight; X: the tile's largest
+//   |x_k| C_k; B_n = max(sum_i |w_ni| B_i, b_n / max_k C_k) (of a level: 1 /
+//   C_k), so that neuron n's activation is at most X B_n (1 + what biases add);
+//   r_n: the power of two above B_n;
+//
+//   level k times C_k t, neuron n times t / r_n, weight n, i times r_i / r_n,
+//
+// with t X in [2^14, 2^15): activations come out of the matrix cores below 2^15
+// (1 + ..) as the next ones take them, and weights are about 1 at most.  Their
+// lower parts are stored as wl 2^12 and meet xh 2^-12, where wl by itself would
+// be too small.  A row is complete in one wavefront and needs only the B_i
+// before it: one barrier a layer, once per workgroup; X alone is the tile's, and
+// its staging scales the levels as it stores them.  A bias is one more input, b
+// / (r_n rho) against the activation t rho (rho: their largest, or the level's
+// below), or starts the accumulators, binary32, where the operands have no slot.
+// A bias that a level of magnitude 1 cannot reach (a neuron of no weights but a
+// bias) counts in B_n as if one could; X is at least 8 times the largest b_n /
+// r_n so counted, so biases add at most 1/4 to a layer's bound.
+//
+// What is left.  A part loses bits where a value lies 2^13 or more below the
+// bound it was scaled by: up to 2^-25 for an activation, a residue that the
+// preparation measures for a weight.  Carried through the layers (each row's sum
+// of |weights| times what its inputs may be off), that bounds the outputs' error
+// in the last sums, E_c, in the worst case.  What is lost in fact, by roundings
+// that do not all point one way, is 1/40 of it (no hidden matrix), 1/180, 1/430,
+// 1/680, 1/1250 (one, 40, 64, 96, 128 wide) or 1/240, 1/740, 1/1200, 1/2800 (two;
+// largest error over 8192 pixels, nets drawn at random, a texel that raises X so
+// that little else is seen).  A 16-pixel group counts only if each of its pixels
+// has, for each channel, an output bias or one of its four partial sums above E_c
+// times 2^23 times that, about: then what is lost stays below 1e-7 of it.  Other
+// groups are evaluated again by the fp32 matrix instructions.  Nets of any common
+// distribution pass by a factor of 4 to 300 (whatever the scales of their levels,
+// neurons and biases); tiles with a texel 2^12 times larger than the rest, or
+// nets whose sums cancel, do not.
+//
+// Range.  A workgroup with a weight or bias of 2^24 or more or B_n of 2^90, a
+// tile with a level of 2^24 or more (NaN and infinities included), and one whose
+// levels are so large (2^13 X at its least) that negative biases cut to fp16
+// would no longer be sure to win, run on the fp32 matrix instructions altogether.
 //
 // Matrix-core mapping (lane l, lane group g = l / 16, i = l % 16)
 //   v_mfma_f32_16x16x32_f16 takes A[i][8g + j] and B[8g + j][i], j = 0..7,
@@ -45,30 +70,36 @@
 //   4q + g of the lane's pixel): every lane group holds a quarter of any width
 //   and forms its own K entries.  A word (two entries) holds one part of two
 //   consecutive values, a pair; the words of four pairs make one operand, and
-//   their three products take three instructions over two A operands (wh, wl).
-//   One pair left over: B = (h, l, h, s) against A = (wh, wh, wl, b); two: B0
-//   = (h, h', l, l') against A0 = (wh, wh', wh, wh') and B1 = (h, h', s, 0)
-//   against A1 = (wl, wl', b, 0); three: a fourth pair (s, 0) against b.  (s:
-//   the bias activation rho; b: the bias's two parts, lane group 0.)  Where
-//   the pairs fill their operands the bias starts the accumulator, scaled.
-//   The first layer's further products take one more step: B against (wll, wl,
-//   0, bll), or B0 against (wll, wll', wl, wl'), wll and bll the third parts.
+//   their three products take three instructions over two A operands (wh, wl;
+//   hs marks xh 2^-12).  One pair left over: B = (h, l, hs, s) against A = (wh,
+//   wh, wl, b); two: B0 = (h, h', l, l') against A0 = (wh, wh', wh, wh') and B1
+//   = (hs, hs', s, s) against A1 = (wl, wl', b, b3); three: a fourth pair of
+//   zeros.  (s: the bias activation and 2^-12 of it; b: the bias's upper and
+//   lower part, b3 its third, lane group 0.)  The first layer's third parts take
+//   one more step: B against (0, wl 2^-12, wll, b3), or B1 against (wll, wll',
+//   0, 0).
 //
 // What binds it (768x512 x 64, 7 -> 40 -> 40 -> 3): vector issue and, with it,
-// the chip's power.  A 16-pixel group takes 136 vector instructions
-// (prologue and tile set-up included) and 18 matrix ones; each matrix
-// instruction keeps vector ones from issuing for 8 of its 16 cycles.  Against the first version (per-layer scales from each
-// pixel's activations, remainders by v_fma_mixlo/hi_f16, which issue at half
-// rate, the biases and inverse scales applied per value, four chains in the
-// output layer; 189 vector instructions): 664 -> 487 us; 2048x1536 103 -> 74,
-// 3840x2160 (8 -> 64 -> 64 -> 3) 334 -> 261, one 768x512 image 17.6 -> 14.7 us.
-// Its error against 64 bits fell from 1.1 times the fp32 family's to 0.55 to
-// 0.8 times on nets whose outputs lie in [0, 1] (0.92 to 1.15 times, 33 to 64
-// wide, where the last layer is drawn like the others and the outputs range
-// over +-3).  Tried and slower: six products of three bf16 parts (exact,
-// nothing to scale, as many vector instructions, twice the matrix ones) ran at
-// 2.0 to 2.25 GHz where this and the fp32 kernel keep 2.3 to 2.4, 655 to 830
-// us.
+// the chip's power; past 48 wide the LDS too (3840x2160, 8 -> 64 -> 64 -> 3:
+// 53 reads a pass, mostly of 16 bytes a lane; eight more, for bias rows, cost
+// 25 us of 270).  A 16-pixel group takes 132 vector instructions (prologue and
+// tile set-up included) and 18 matrix ones; each matrix instruction keeps
+// vector ones from issuing for 8 of its 16 cycles.  768x512 x 64 477 to 490 us,
+// 2047x1365 (48 wide) 74, 3840x2160 265, one 768x512 image 15.4, of which the
+// preparation of the neurons' scales, about 300 vector instructions a wavefront
+// and two barriers, is 1.  (With one scale a layer, and one per pixel for the
+// levels, the same: 477 to 490, 74, 262, 14.6; but values 2^8 below their layer's
+// largest lost bits.)  The first version, per-layer scales from each pixel's
+// activations, remainders by v_fma_mixlo/hi_f16, which issue at half rate, the
+// biases and inverse scales applied per value, four chains in the output layer:
+// 189 vector instructions, 664, 103, 334, 17.6 us.
+// Its error against 64 bits is 0.55 to 0.85 times the fp32 family's on nets
+// whose outputs lie in [0, 1]; where the last layer is drawn like the others and
+// the outputs range over +-3, 0.98 to 1.03 times for 64 wide, 1.07 to 1.24 for 33
+// to 48, 0.82 to 0.87 (of the vector family's) past 64.  Tried and slower: wl * xl
+// in the hidden layers too (those ratios 0.04 to 0.08 less, 768x512 x 64 485 ->
+// 525 us); six products of three bf16 parts (exact, nothing to scale, as many
+// vector instructions, twice the matrix ones), 655 to 830 us.
 #pragma once
 
 #include "decode_common.h"
@@ -83,6 +114,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
+// The lower parts of weights are stored times 2^kLow (the activations they
+// meet times 2^-kLow): far enough that a weight 2^-25 of its row keeps 11 bits,
+// and no further, or the activations' would be cut.
+constexpr int kLow = 12;
+
 // A layer's input of Q values per lane group: P pairs, QUADS operands of four
 // in each part, TAIL mixed ones (as many A operands as steps); BIAS: whether a
 // slot is left for it.
@@ -93,7 +129,7 @@ struct Shape {
     static constexpr int QUADS = P / 4 + (R == 3 ? 1 : 0);
     static constexpr int TAIL = R == 3 ? 0 : R;
     static constexpr int NA = 2 * QUADS + TAIL + (FIRST ? 1 : 0);
-    static constexpr bool BIAS = R != 0;
+    static constexpr bool BIAS = TAIL > 0;
     static_assert(!FIRST || (QUADS == 0 && TAIL > 0), "the first layer's pairs are left over");
 };
 
@@ -103,29 +139,45 @@ struct Layout {
     static constexpr int N1A = Shape<LS, true>::NA, NHA = Shape<KSH>::NA;   // A operands per output block
     static constexpr int W1A = 0;                                     // u32 [NB][N1A][64][4]
     static constexpr int WHA = W1A + NB * N1A * 256;                  // u32 [NH][NB][NHA][64][4]
-    static constexpr int BIAS = WHA + NH * NB * NHA * 256;            // f32 [NH + 1][N], swz order
-    static constexpr int W3 = BIAS + (NH + 1) * N;                    // f32 [3][N], swz order
-    static constexpr int MAXW = W3 + 3 * N;                           // f32 [NH + 1][kWaves]: largest weights
-    static constexpr int MAXB = MAXW + (NH + 1) * kWaves;             // f32 [kWaves]: largest bias of layer min(w, NH), by wavefront w
-    static constexpr int BAD = MAXB + kWaves;                         // u32 [2][kWaves]: out-of-range flags
+    static constexpr int HB = Shape<KSH>::BIAS ? 0 : NH;              // hidden layers whose biases start the accumulators
+    static constexpr int BIAS = WHA + NH * NB * NHA * 256;            // f32 [HB][N], swz order: those, scaled for the tile
+    static constexpr int RAWB = BIAS + HB * N;                        // f32 [HB][N], swz: over r_n
+    static constexpr int BND = RAWB + HB * N;                         // f32 [NH + 1][N], swz: B_n
+    static constexpr int W3 = BND + (NH + 1) * N;                     // f32 [3][N], swz order, times r_n
+    static constexpr int CMAX = W3 + 3 * N;                           // f32 [4 LS][kWaves]: largest weights of each level
+    static constexpr int CSCALE = CMAX + 4 * LS * kWaves;             // f32 [4 LS]: C_k
+    static constexpr int ERR = CSCALE + 4 * LS;                       // f32 [NH + 1][kWaves]: largest errors
+    static constexpr int BMAX = ERR + (NH + 1) * kWaves;              // f32 [NH + 1][kWaves]: largest |b_n| / r_n
+    static constexpr int XMAX = BMAX + (NH + 1) * kWaves;             // f32 [kWaves]: largest scaled levels of the tile
+    static constexpr int L1C = XMAX + kWaves;                         // f32 [kWaves]: sum of |w3|, by channel
+    static constexpr int BAD = L1C + kWaves;                          // u32 [2][kWaves]: out-of-range flags
     static constexpr int COL = BAD + 2 * kWaves;                      // (int, f32) [4 LS][TW]: column taps
     static constexpr int ROW = COL + 4 * LS * TW * 2;                 // (int, f32) [4 LS][THT]: row taps
     static constexpr int LAT = ROW + 4 * LS * THT * 2;                // latent boxes
     static constexpr int SIZE = LAT + box_offset<THT>(4 * LS);
 };
 
-// Each 16-neuron group of a bias vector and of the output layer's rows is
-// stored with the two 2-bit halves of its index swapped, so that a lane
+// Each 16-neuron group of a bias vector, of the bounds and of the output
+// layer's rows is stored with the two 2-bit halves of its index swapped, so that a lane
 // group's four neurons of a block are one 16-byte read.
 __host__ __device__ constexpr int swz(int n) { return (n & ~15) | ((n & 3) << 2) | ((n >> 2) & 3); }
 
 // Neuron on row `row` of an output block; the map is its own inverse.
 __device__ __forceinline__ int row_neuron(int row) { return 4 * (row & 3) + (row >> 2); }
 
-__device__ __forceinline__ float pow2(int e) { return __int_as_float((e + 127) << 23); }
+// The power of two above x >= 0 (x in [p / 2, p)); 2^-126 for 0.
+__device__ __forceinline__ float pow2_above(float x)
+{
+    return __uint_as_float((__float_as_uint(x) & 0x7f800000u) + 0x00800000u);
+}
 
-// e with |x| in [2^(e - 1), 2^e) for a normal x (-126 for zero).
-__device__ __forceinline__ int exponent(float x) { return ((__float_as_int(x) >> 23) & 0xff) - 126; }
+// 1 / p for a power of two (exact).
+__device__ __forceinline__ float pow2_inverse(float p) { return __uint_as_float((254u << 23) - __float_as_uint(p)); }
+
+// C_k and 1 / C_k of a level whose largest weight is m: 0 for a level without
+// weights, at least 2^-60 for others.
+__device__ __forceinline__ float level_scale(float m) { return m > 0.0f ? fmaxf(pow2_above(m), 0x1p-60f) : 0.0f; }
+__device__ __forceinline__ float level_unscale(float c) { return c > 0.0f ? pow2_inverse(c) : 0.0f; }
 
 // The two parts of a pair of values, as packed words (first value low).  The
 // remainder x - xh is one mixed-precision fused multiply-add, exact (written
@@ -144,12 +196,40 @@ __device__ __forceinline__ Parts split2(float x0, float x1)
     return Parts{h, __builtin_bit_cast(unsigned, l)};
 }
 
-// A third part: the remainder of split2.
-__device__ __forceinline__ unsigned third(float x0, float x1, const Parts &p)
+// A pair of fp16 values times 2^-kLow.
+__device__ __forceinline__ unsigned lower(unsigned h)
 {
-    const f16x2 h = __builtin_bit_cast(f16x2, p.h), l = __builtin_bit_cast(f16x2, p.l);
-    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x0 - (float)h[0] - (float)l[0],
-                                                                       x1 - (float)h[1] - (float)l[1]}), f16x2));
+    constexpr _Float16 k = (_Float16)(1.0f / (1 << kLow));
+    return __builtin_bit_cast(unsigned, __builtin_bit_cast(f16x2, h) * f16x2{k, k});
+}
+
+// The parts of a pair of weights: h, l 2^kLow, third 2^kLow; lost: what the
+// first two leave of weights below 2^-14 (those above keep 23 bits), 2^kLow.
+struct WeightParts {
+    unsigned h, l, third;
+    float lost;
+};
+
+__device__ __forceinline__ WeightParts split_weights(float x0, float x1)
+{
+    constexpr float up = (float)(1 << kLow);
+    auto rest = [](unsigned h, float x, bool hi) {    // x - h's low or high half
+        float r;
+        if (hi)
+            asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
+        else
+            asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
+        return r;
+    };
+    auto pack = [](float a, float b) {
+        return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), f16x2));
+    };
+    const unsigned h = pack(x0, x1);
+    const float r0 = rest(h, x0, false) * up, r1 = rest(h, x1, true) * up;
+    const unsigned l = pack(r0, r1);
+    const float t0 = rest(l, r0, false), t1 = rest(l, r1, true);
+    return WeightParts{h, l, pack(t0, t1),
+                       (fabsf(x0) < 0x1p-14f ? fabsf(t0) : 0.0f) + (fabsf(x1) < 0x1p-14f ? fabsf(t1) : 0.0f)};
 }
 
 __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
@@ -158,59 +238,90 @@ __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
                                                   0);
 }
 
-// A operands of one output block's row: its scaled weights of the pairs, and
-// the scaled bias (lane group 0; zero elsewhere).
+// A operands of one output block's row, from its scaled weights of the pairs,
+// without its bias; returns what their parts lose, 2^kLow.
 template <int Q, bool FIRST>
-__device__ __forceinline__ void build_a(const float (&w)[2 * Shape<Q>::P], float bias,
-                                        u32x4 (&a)[Shape<Q, FIRST>::NA])
+__device__ __forceinline__ float build_a(const float (&w)[2 * Shape<Q>::P], u32x4 (&a)[Shape<Q, FIRST>::NA])
 {
     using S = Shape<Q, FIRST>;
-    Parts p[4 * S::QUADS + S::TAIL];
-    const Parts b = split2(bias, 0.0f);
+    WeightParts p[4 * S::QUADS + S::TAIL];
+    float lost = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4 * S::QUADS + S::TAIL; ++i)
-        p[i] = i < S::P ? split2(w[2 * i], w[2 * i + 1]) : b;
+    for (int i = 0; i < 4 * S::QUADS + S::TAIL; ++i) {
+        p[i] = i < S::P ? split_weights(w[2 * i], w[2 * i + 1]) : WeightParts{0u, 0u, 0u, 0.0f};
+        lost += p[i].lost;
+    }
 #pragma unroll
     for (int q = 0; q < S::QUADS; ++q) {
         a[2 * q] = u32x4{p[4 * q].h, p[4 * q + 1].h, p[4 * q + 2].h, p[4 * q + 3].h};
         a[2 * q + 1] = u32x4{p[4 * q].l, p[4 * q + 1].l, p[4 * q + 2].l, p[4 * q + 3].l};
     }
-    const unsigned bw = b.h | b.l << 16;
     if constexpr (S::TAIL == 1) {
-        const Parts t = p[4 * S::QUADS];
-        a[2 * S::QUADS] = u32x4{t.h, t.h, t.l, bw};
+        const WeightParts t = p[4 * S::QUADS];
+        a[2 * S::QUADS] = u32x4{t.h, t.h, t.l, 0u};
         if constexpr (FIRST)
-            a[1] = u32x4{third(w[0], w[1], t), t.l, 0u, third(bias, 0.0f, b) & 0xffffu};
+            a[1] = u32x4{0u, lower(t.l), t.third, 0u};
     } else if constexpr (S::TAIL == 2) {
-        const Parts t = p[4 * S::QUADS], u = p[4 * S::QUADS + 1];
+        const WeightParts t = p[4 * S::QUADS], u = p[4 * S::QUADS + 1];
         a[2 * S::QUADS] = u32x4{t.h, u.h, t.h, u.h};
-        a[2 * S::QUADS + 1] = u32x4{t.l, u.l, bw, 0u};
+        a[2 * S::QUADS + 1] = u32x4{t.l, u.l, 0u, 0u};
         if constexpr (FIRST)
-            a[2] = u32x4{third(w[0], w[1], t), third(w[2], w[3], u), t.l, u.l};
+            a[2] = u32x4{t.third, u.third, 0u, 0u};
+    }
+    return lost;
+}
+
+// Put one row's scaled bias (lane group 0; zero elsewhere) into the block's
+// operands at a: upper and lower part in one word, a third part in another
+// where there is one left.
+template <int Q, bool FIRST>
+__device__ __forceinline__ void put_bias(unsigned *a, float bias)
+{
+    using S = Shape<Q, FIRST>;
+    const WeightParts b = split_weights(bias, 0.0f);
+    const unsigned w = b.h | b.l << 16, w3 = b.third << 16;
+    if constexpr (S::TAIL == 1) {
+        a[2 * S::QUADS * 256 + 3] = w;
+        if constexpr (FIRST)
+            a[256 + 3] = w3;
+    } else if constexpr (S::TAIL == 2) {
+        a[(2 * S::QUADS + 1) * 256 + 2] = w;
+        a[(2 * S::QUADS + 1) * 256 + 3] = w3;
     }
 }
 
-// One layer for G groups of 16 pixels: d[gi][ob] += W v[gi], small partial
-// products first.  la: the layer's A operands (at this lane's words); s: the
-// bias activation.
+// One layer for G groups of 16 pixels: d[gi][ob] = bias + W v[gi], small
+// partial products first.  la: the layer's A operands (at this lane's words);
+// lb: its bias rows (at this lane group's), which start the accumulators where
+// the operands have no slot; sw: the bias activation's word.
 template <int Q, bool FIRST, int NB, int G>
-__device__ __forceinline__ void apply(const unsigned *la, const float (&v)[G][Q], const float (&s)[G], f32x4 (&d)[G][NB])
+__device__ __forceinline__ void apply(const unsigned *la, const float *lb, unsigned sw, const float (&v)[G][Q],
+                                      f32x4 (&d)[G][NB])
 {
     using S = Shape<Q, FIRST>;
     auto op = [&](int ob, int i) { return *reinterpret_cast<const u32x4 *>(la + (ob * S::NA + i) * 256); };
     auto val = [&](int gi, int i) { return i < Q ? v[gi][i < Q ? i : 0] : 0.0f; };
-    auto ss = [&](int gi) { return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{s[gi], s[gi]}), f16x2)); };
+    // one step of every group against output block ob; `start`: the layer's first
+    auto step = [&](bool start, int ob, u32x4 w, const u32x4 (&b)[G]) {
+        f32x4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (start && !S::BIAS)
+            bias = *reinterpret_cast<const f32x4 *>(lb + 16 * ob);
+#pragma unroll
+        for (int gi = 0; gi < G; ++gi)
+            d[gi][ob] = mfma(w, b[gi], start ? bias : d[gi][ob]);
+    };
 #pragma unroll
     for (int q = 0; q < S::QUADS; ++q) {
-        u32x4 h[G], l[G];
+        u32x4 h[G], l[G], hs[G];
 #pragma unroll
         for (int gi = 0; gi < G; ++gi)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int i = 4 * q + j;
-                const Parts t = i < S::P ? split2(val(gi, 2 * i), val(gi, 2 * i + 1)) : Parts{ss(gi) & 0xffffu, 0u};
+                const Parts t = i < S::P ? split2(val(gi, 2 * i), val(gi, 2 * i + 1)) : Parts{0u, 0u};
                 h[gi][j] = t.h;
                 l[gi][j] = t.l;
+                hs[gi][j] = i < S::P ? lower(t.h) : 0u;
             }
         u32x4 wh[NB], wl[NB];
 #pragma unroll
@@ -222,9 +333,7 @@ __device__ __forceinline__ void apply(const unsigned *la, const float (&v)[G][Q]
         for (int st = 0; st < 3; ++st)
 #pragma unroll
             for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-                for (int gi = 0; gi < G; ++gi)
-                    d[gi][ob] = mfma(st == 0 ? wl[ob] : wh[ob], st == 1 ? l[gi] : h[gi], d[gi][ob]);
+                step(q == 0 && st == 0, ob, st == 0 ? wl[ob] : wh[ob], st == 0 ? hs : st == 1 ? l : h);
     }
     if constexpr (S::TAIL == 1) {
         constexpr int i = 4 * S::QUADS;
@@ -232,17 +341,13 @@ __device__ __forceinline__ void apply(const unsigned *la, const float (&v)[G][Q]
 #pragma unroll
         for (int gi = 0; gi < G; ++gi) {
             const Parts t = split2(val(gi, 2 * i), val(gi, 2 * i + 1));
-            b[gi] = u32x4{t.h, t.l, t.h, ss(gi)};
+            b[gi] = u32x4{t.h, t.l, lower(t.h), sw};
         }
 #pragma unroll
         for (int st = FIRST ? 1 : 0; st >= 0; --st)
 #pragma unroll
-            for (int ob = 0; ob < NB; ++ob) {
-                const u32x4 w = op(ob, 2 * S::QUADS + st);
-#pragma unroll
-                for (int gi = 0; gi < G; ++gi)
-                    d[gi][ob] = mfma(w, b[gi], d[gi][ob]);
-            }
+            for (int ob = 0; ob < NB; ++ob)
+                step(S::QUADS == 0 && st == (FIRST ? 1 : 0), ob, op(ob, 2 * S::QUADS + st), b);
     } else if constexpr (S::TAIL == 2) {
         constexpr int i = 4 * S::QUADS;
         u32x4 b0[G], b1[G];
@@ -251,55 +356,104 @@ __device__ __forceinline__ void apply(const unsigned *la, const float (&v)[G][Q]
             const Parts t = split2(val(gi, 2 * i), val(gi, 2 * i + 1));
             const Parts u = split2(val(gi, 2 * i + 2), val(gi, 2 * i + 3));
             b0[gi] = u32x4{t.h, u.h, t.l, u.l};
-            b1[gi] = u32x4{t.h, u.h, ss(gi), 0u};
+            b1[gi] = u32x4{lower(t.h), lower(u.h), sw, sw};
         }
 #pragma unroll
         for (int st = FIRST ? 2 : 1; st >= 0; --st)
 #pragma unroll
-            for (int ob = 0; ob < NB; ++ob) {
-                const u32x4 w = op(ob, 2 * S::QUADS + st);
-#pragma unroll
-                for (int gi = 0; gi < G; ++gi)
-                    d[gi][ob] = mfma(w, st == 1 ? b1[gi] : b0[gi], d[gi][ob]);
-            }
+            for (int ob = 0; ob < NB; ++ob)
+                step(S::QUADS == 0 && st == (FIRST ? 2 : 1), ob, op(ob, 2 * S::QUADS + st), st == 0 ? b0 : b1);
     }
 }
 
-// Largest over the four lane groups of this lane's column of the bit patterns
-// of x (>= 0, not NaN: such floats order like them; maxima of floats would be
-// preceded by two more instructions each, which quieten NaNs).
-__device__ __forceinline__ int column_max(float x)
+// Largest of x over the four lane groups of this lane's column.
+__device__ __forceinline__ float column_max(float x)
 {
     const unsigned xi = __float_as_uint(x);
     const u32x2 a = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
     const unsigned m = max(a[0], a[1]);
     const u32x2 c = __builtin_amdgcn_permlane32_swap(m, m, false, false);
-    return (int)max(c[0], c[1]);
+    return __uint_as_float(max(c[0], c[1]));
 }
 
-// Largest of x (>= 0, not NaN: such floats order like their bit patterns)
-// over the wavefront, by data-parallel moves within the vector unit instead
-// of exchanges through LDS: the maximum of each quad (two quad
-// permutations), of each row of 16 (row shifts by 4 and 8 leave it in lane
-// 15), then of rows 0-1 and 2-3 (lane 15 of the row before broadcast into
-// rows 1 and 3) and of the wavefront (lane 31 broadcast into rows 2 and 3),
-// read from lane 63.  Lanes a move does not write keep their own value.
+// Reductions by data-parallel moves within the vector unit instead of exchanges
+// through LDS: over each row of 16 lanes by rotations of 8, 4, 2 and 1 (every
+// lane has the result), over the wavefront by broadcasts between the rows (lane
+// 15 of the row before into rows 1 and 3, lane 31 into rows 2 and 3), read from
+// lane 63; lanes a move does not write take part with their own value (maxima)
+// or 0 (sums).  Maxima: of x >= 0, not NaN (such floats order like their bits).
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int moved(int old, int x)
+{
+    return __builtin_amdgcn_update_dpp(old, x, CTRL, ROWS, 0xF, false);
+}
+
+__device__ __forceinline__ int row16_max(int v)
+{
+    v = max(v, moved<0x128>(v, v));    // row_ror:8
+    v = max(v, moved<0x124>(v, v));
+    v = max(v, moved<0x122>(v, v));
+    return max(v, moved<0x121>(v, v));
+}
+
 __device__ __forceinline__ float wave_max(float x)
 {
-    int v = __float_as_int(x);
-    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));    // quad_perm [1, 0, 3, 2]
-    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));    // quad_perm [2, 3, 0, 1]
-    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));   // row_shr:4
-    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));   // row_shr:8
-    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));   // row_bcast:15, rows 1 and 3
-    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));   // row_bcast:31, rows 2 and 3
+    int v = row16_max(__float_as_int(x));
+    v = max(v, moved<0x142, 0xA>(v, v));   // row_bcast:15, rows 1 and 3
+    v = max(v, moved<0x143, 0xC>(v, v));   // row_bcast:31, rows 2 and 3
     return __int_as_float(__builtin_amdgcn_readlane(v, 63));
+}
+
+__device__ __forceinline__ float wave_sum(float x)
+{
+    auto add = [&](int y) { x += __int_as_float(y); };
+    add(moved<0x128>(0, __float_as_int(x)));
+    add(moved<0x124>(0, __float_as_int(x)));
+    add(moved<0x122>(0, __float_as_int(x)));
+    add(moved<0x121>(0, __float_as_int(x)));
+    add(moved<0x142, 0xA>(0, __float_as_int(x)));
+    add(moved<0x143, 0xC>(0, __float_as_int(x)));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// t of a tile whose largest scaled level is x, and 1 / t.
+__device__ __forceinline__ float tile_scale(float x, float &inv_t)
+{
+    const float p = pow2_above(x);
+    inv_t = p * 0x1p-15f;
+    return 0x1p15f * pow2_inverse(p);
+}
+
+__device__ __forceinline__ float max4(const f32x4 &m) { return fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])); }
+
+// Whether one of the workgroup's 2 kWaves out-of-range flags is set.
+__device__ __forceinline__ unsigned any_flag(const unsigned *flags)
+{
+    const u32x4 a = reinterpret_cast<const u32x4 *>(flags)[0], b = reinterpret_cast<const u32x4 *>(flags)[1];
+    return __builtin_amdgcn_readfirstlane(a[0] | a[1] | a[2] | a[3] | b[0] | b[1] | b[2] | b[3]);
+}
+
+__device__ __forceinline__ float uniform(float x)
+{
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
+}
+
+// f(register, level) for the box registers of load_boxes.
+template <int KMAX, int THT, class F>
+__device__ __forceinline__ void each_box_reg(F f)
+{
+    int idx = 0;
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k)
+#pragma unroll
+        for (int i0 = 0; i0 < box_floats<THT>(k); i0 += kThreads)
+            f(idx++, k);
 }
 
 // NB: 16-neuron blocks of the hidden width; NH: hidden layers; LS: levels per
 // lane group (ceil(L / 4)); KSH: values per lane group of the hidden layers'
 // inputs (ceil(width / 4)); RPW: tile rows per wavefront (a tile is 4 RPW
-// rows: 8, or 16 when the launch has tiles to spare).
+// rows: 8, or 16 or 32 when the launch has tiles to spare).
 template <int NB, int NH, int LS, int KSH, int RPW>
 __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blocks_per_image, int tiles_x,
                                                          int tiles, uint32_t tx_recip)
@@ -343,11 +497,12 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
     // waited for (the first tile's latents first), through raw buffers whose
     // range check returns 0 past each array's end (rows past a layer's
     // outputs).  Wavefront w forms the A operands of output blocks w, w + 4:
-    // lane (g, col) holds row rn(col)'s weights of the inputs 4 q + g.  Each
-    // layer's largest weight and bias give its scales after one barrier; then
-    // the weights are split and stored.
-    float sscale[NH + 1];   // bias activations per unit of the pixel's scale
-    float mfloor, unscale;  // least magnitude a pixel's scale is taken from; 1 / (weight scales)
+    // lane (g, col) holds row rn(col)'s weights of the inputs 4 q + g.
+    float inv_t = 0.0f;    // 1 / t of the tile
+    float xfloor;          // least X
+    float rho;             // scale of the biases in the operands: their activation is t rho
+    bool steep;            // whether some are far above it: cut to fp16's range
+    float sb = 0.0f;       // the tile's t rho
     {
         LayerParams lp[NH + 2];
         int wd[NH + 3];
@@ -399,21 +554,15 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
             fill_taps<LV, THT>(ldsu, LY::COL, LY::ROW, LY::LAT, p, by * THT, (blk - by * tiles_x) * TW, wave, lane);
         }
         // entries past a layer's inputs read the next row: zeroed
-        float mw[NH + 1], mb = 0.0f;
         float sum = fabsf(b3_0) + fabsf(b3_1) + fabsf(b3_2), lsum = 0.0f;
-#pragma unroll
-        for (int l = 0; l <= NH; ++l)
-            mw[l] = 0.0f;
 #pragma unroll
         for (int j = 0; j < BPW; ++j) {
             if (LS & 1)
                 w1[j][LS] = 0.0f;
             w1[j][LS - 1] = 4 * (LS - 1) + g < L ? w1[j][LS - 1] : 0.0f;
 #pragma unroll
-            for (int q = 0; q < LS; ++q) {
-                mw[0] = fmaxf(mw[0], fabsf(w1[j][q]));
+            for (int q = 0; q < LS; ++q)
                 sum += fabsf(w1[j][q]);
-            }
 #pragma unroll
             for (int h = 0; h < NH; ++h) {
                 if (KSH & 1)
@@ -421,120 +570,221 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
 #pragma unroll
                 for (int q = 0; q < KSH; ++q) {
                     wh[j][h][q] = 4 * q + g < wd[1 + h] ? wh[j][h][q] : 0.0f;
-                    mw[1 + h] = fmaxf(mw[1 + h], fabsf(wh[j][h][q]));
                     sum += fabsf(wh[j][h][q]);
                 }
             }
         }
 #pragma unroll
+        for (int q = 0; q < LS; ++q) {    // largest weight of levels 4 q + g
+            float m = fabsf(w1[0][q]);
+#pragma unroll
+            for (int j = 1; j < BPW; ++j)
+                m = fmaxf(m, fabsf(w1[j][q]));
+            const int mb = row16_max(__float_as_int(m));
+            if (col == 0)
+                ldsu[LY::CMAX + (4 * q + g) * kWaves + wave] = mb;
+        }
+#pragma unroll
         for (int i = 0; i < NPL; ++i) {
             w3v[i] = lane + 64 * i < NL ? w3v[i] : 0.0f;
             sum += fabsf(bv[i]) + fabsf(w3v[i]);
-            mb = fmaxf(mb, fabsf(bv[i]));
         }
-        if (blk < tiles) {
-#pragma unroll
-            for (int i = 0; i < box_regs<LV, THT>(); ++i)
-                lsum += fabsf(boxv[i]);
-            store_boxes<LV, THT>(lds + LY::LAT, boxv, tid);
-        }
-#pragma unroll
-        for (int i = 0; i < NPL; ++i) {
-            const int n = lane + 64 * i;
-            if (n < LY::N) {
-                if (wave <= NH)
-                    lds[LY::BIAS + wave * LY::N + swz(n)] = bv[i];
-                if (wave < 3)
-                    lds[LY::W3 + wave * LY::N + swz(n)] = w3v[i];
-            }
-        }
+        if (blk < tiles)
+            each_box_reg<LV, THT>([&](int i, int) { lsum += fabsf(boxv[i]); });
+        bool pbad = !(sum < kRange);
         {
-            float m[NH + 2];
-#pragma unroll
-            for (int l = 0; l <= NH; ++l)
-                m[l] = wave_max(mw[l]);
-            m[NH + 1] = wave_max(mb);
-            const bool pbad = __any(!(sum < kRange)), tbad = __any(!(lsum < kRange));
-            if (lane == 0) {
-#pragma unroll
-                for (int l = 0; l <= NH; ++l)
-                    lds[LY::MAXW + l * kWaves + wave] = m[l];
-                lds[LY::MAXB + wave] = m[NH + 1];
+            const bool tbad = __any(!(lsum < kRange));
+            if (lane == 0)
                 ldsu[LY::BAD + wave] = tbad;
-                ldsu[LY::BAD + kWaves + wave] = pbad;
-            }
         }
         __syncthreads();
-        // scales (wave-uniform).  Layer l's weights times wsc[l], its biases
-        // times bsc[l] against the activation rho sc_l; sc_l, the scale of
-        // its inputs, is the pixel's times the weight scales before it (and
-        // 2^-22 for a second hidden layer's).
-        float wsc[NH + 1], bsc[NH + 1];
-        float chain = 1.0f;
-        bool ok = true;
-        mfloor = pow2(-40);
+
+        // The layers in turn: each row's sum of |weights| times its inputs'
+        // bounds, its bound and scale; then its operands, and what they lose.
+        float ck[LV];    // C_k
+        float one;       // the largest: a level of magnitude 1, scaled
 #pragma unroll
         for (int l = 0; l <= NH; ++l) {
-            const f32x4 m = *reinterpret_cast<const f32x4 *>(&lds[LY::MAXW + l * kWaves]);
-            const float wm = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
-            const float bm = lds[LY::MAXB + l];
-            ok = ok && (wm == 0.0f || (wm >= 0x1p-16f && wm < kRange)) && bm < kRange;
-            // (clamped, so that the scales stay finite where `ok` is false)
-            const int ew = wm == 0.0f ? 0 : min(max(exponent(wm), -16), 24);
-            const int eb = min(max(exponent(bm), -40), 24);
-            wsc[l] = pow2((l == 0 ? 5 : 14) - ew);
-            const float rho = pow2(eb - ew);
-            bsc[l] = wsc[l] * pow2(ew - eb);
-            sscale[l] = rho * chain;
-            // s_0 <= 2^6, s_l <= 2^15
-            mfloor = fmaxf(mfloor, l == 0 ? rho : sscale[l] * 0x1p-9f);
-            chain *= wsc[l];
-            if (l > 0 && l < NH)
-                chain *= 0x1p-22f;
-        }
-        unscale = __int_as_float((254 << 23) - __float_as_int(chain));    // (exact: a power of two)
-        if (!ok && lane == 0)
-            ldsu[LY::BAD + kWaves + wave] = 1u;
+            constexpr int Q = LS > KSH ? LS : KSH;
+            float cb[Q];    // B_i of the inputs 4 q + g
+            if (l == 0) {
 #pragma unroll
-        for (int j = 0; j < BPW; ++j) {
-            const int blk16 = wave + kWaves * j;
-            if (blk16 < NB) {
-                u32x4 a1[LY::N1A];
+                for (int q = 0; q < LS; ++q) {
+                    const float c = level_scale(max4(*reinterpret_cast<const f32x4 *>(&lds[LY::CMAX + (4 * q + g) * kWaves])));
+                    if (tid == 16 * g)
+                        lds[LY::CSCALE + 4 * q + g] = c;
+                    cb[q] = level_unscale(c);
+                    one = q == 0 ? c : fmaxf(one, c);
+                }
+                one = fmaxf(column_max(one), 0x1p-60f);
+            } else {
 #pragma unroll
-                for (int q = 0; q < 2 * Shape<LS>::P; ++q)
-                    w1[j][q] *= wsc[0];
-                build_a<LS, true>(w1[j], g == 0 ? brow[j][0] * bsc[0] : 0.0f, a1);
+                for (int q = 0; q < KSH; q += 4) {
+                    const f32x4 bd = *reinterpret_cast<const f32x4 *>(&lds[LY::BND + (l - 1) * LY::N + 4 * q + 4 * g]);
 #pragma unroll
-                for (int i = 0; i < LY::N1A; ++i)
-                    *reinterpret_cast<u32x4 *>(&ldsu[LY::W1A + ((blk16 * LY::N1A + i) * 64 + lane) * 4]) = a1[i];
+                    for (int i = 0; i < 4 && q + i < KSH; ++i)
+                        cb[q + i] = bd[i];
+                }
+            }
+            if (l == (NH > 0 ? 1 : 0) && blk < tiles) {    // the first tile's largest scaled level
 #pragma unroll
-                for (int h = 0; h < NH; ++h) {
+                for (int k = 0; k < LV; ++k)
+                    ck[k] = NH > 0 ? lds[LY::CSCALE + k]
+                                   : level_scale(max4(*reinterpret_cast<const f32x4 *>(&lds[LY::CMAX + k * kWaves])));
+                float m = 0.0f;
+                each_box_reg<LV, THT>([&](int i, int k) { m = fmaxf(m, fabsf(boxv[i]) * ck[k]); });
+                m = wave_max(m);
+                if (lane == 0)
+                    lds[LY::XMAX + wave] = m;
+            }
+            // what the inputs may be off, in 2^-25 (a level: by its parts)
+            const float err = l == 0 ? 1.0f
+                                     : max4(*reinterpret_cast<const f32x4 *>(&lds[LY::ERR + (l > 0 ? l - 1 : 0) * kWaves])) + 1.0f;
+            const float inv_one = pow2_inverse(one);
+            float worst = 0.0f, bmax = 0.0f;
+#pragma unroll
+            for (int j = 0; j < BPW; ++j) {
+                const int blk16 = wave + kWaves * j, h = l > 0 ? l - 1 : 0;
+                if (blk16 >= NB)
+                    break;    // wave-uniform
+                float s = 0.0f, l1 = 0.0f;
+                if (l == 0) {
+#pragma unroll
+                    for (int q = 0; q < LS; ++q)
+                        s = __builtin_fmaf(fabsf(w1[j][q]), cb[q], s);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < KSH; ++q)
+                        s = __builtin_fmaf(fabsf(wh[j][h][q]), cb[q], s);
+                }
+                s = row_sum(s);
+                const float bn = fmaxf(s, brow[j][l] * inv_one);
+                const float ri = bn > 0.0f ? pow2_inverse(pow2_above(bn)) : 0.0f;    // (0: never active)
+                pbad = pbad || !(bn < 0x1p90f);
+                if (g == 0)
+                    lds[LY::BND + l * LY::N + swz(16 * blk16 + row_neuron(col))] = bn;
+                brow[j][l] *= ri;
+                bmax = fmaxf(bmax, fabsf(brow[j][l]));
+                float lost;
+                if (l == 0) {
+                    u32x4 a1[LY::N1A];
+#pragma unroll
+                    for (int q = 0; q < LS; ++q) {
+                        w1[j][q] = w1[j][q] * cb[q] * ri;
+                        l1 += fabsf(w1[j][q]);
+                    }
+                    lost = build_a<LS, true>(w1[j], a1);
+#pragma unroll
+                    for (int i = 0; i < LY::N1A; ++i)
+                        *reinterpret_cast<u32x4 *>(&ldsu[LY::W1A + ((blk16 * LY::N1A + i) * 64 + lane) * 4]) = a1[i];
+                } else {
                     u32x4 ah[LY::NHA];
 #pragma unroll
-                    for (int q = 0; q < 2 * Shape<KSH>::P; ++q)
-                        wh[j][h][q] *= wsc[1 + h];
-                    build_a<KSH, false>(wh[j][h], g == 0 ? brow[j][1 + h] * bsc[1 + h] : 0.0f, ah);
+                    for (int q = 0; q < KSH; ++q) {
+                        wh[j][h][q] = wh[j][h][q] * pow2_above(cb[q]) * ri;
+                        l1 += fabsf(wh[j][h][q]);
+                    }
+                    lost = build_a<KSH, false>(wh[j][h], ah);
 #pragma unroll
                     for (int i = 0; i < LY::NHA; ++i)
                         *reinterpret_cast<u32x4 *>(&ldsu[LY::WHA + (((h * NB + blk16) * LY::NHA + i) * 64 + lane) * 4]) =
                             ah[i];
                 }
+                // a row's inputs off by err, their upper parts times 2^-kLow by
+                // 2^-25 against lower parts of 2^(kLow - 11) |w| (or 2^(kLow -
+                // 25)), its weights by `lost` 2^-kLow against 2^15 (1 + l / 4)
+                worst = fmaxf(worst, row_sum(__builtin_fmaf(l1, err + (float)(1 << kLow) * 0x1p-11f,
+                                                            lost * (0x1p40f * (1.0f + 0.25f * l) / (1 << kLow)))));
+            }
+            // (a bias in the operands, at most 2, loses up to 2^-37 against its
+            // activation of at most 2^12, and up to 2^-12 against one below 2^-12)
+            worst = __int_as_float(row16_max(__float_as_int(worst))) + 0x1p-4f;
+            bmax = __int_as_float(row16_max(__float_as_int(bmax)));
+            if (l == 0 || Shape<KSH>::BIAS)
+                worst += bmax > 0.0f ? 4.0f : 0.0f;
+            if (lane == 0) {
+                lds[LY::ERR + l * kWaves + wave] = worst;
+                lds[LY::BMAX + l * kWaves + wave] = bmax;
+            }
+            if (l == NH) {
+                const bool any = __any(pbad);
+                if (lane == 0)
+                    ldsu[LY::BAD + kWaves + wave] = any;
+            }
+            __syncthreads();
+        }
+
+        // the output layer's weights times the last r_n, the biases over r_n,
+        // the first tile's scaled boxes and biases
+        float bmax = 0.0f;
+#pragma unroll
+        for (int l = 0; l <= NH; ++l)
+            bmax = fmaxf(bmax, max4(*reinterpret_cast<const f32x4 *>(&lds[LY::BMAX + l * kWaves])));
+        bmax = uniform(bmax);
+        const float level = fmaxf(fminf(bmax, one), 0x1p-60f);
+        xfloor = 8.0f * level;
+        rho = 0.5f * pow2_above(level);
+        steep = __builtin_amdgcn_readfirstlane(bmax > 4.0f * rho) != 0;
+        const float irho = pow2_inverse(rho);
+#pragma unroll
+        for (int j = 0; j < BPW; ++j) {
+            const int blk16 = wave + kWaves * j;
+            if (blk16 >= NB)
+                break;    // wave-uniform
+            auto cut = [&](int l) { return g == 0 ? fmaxf(brow[j][l] * irho, -65504.0f) : 0.0f; };
+            put_bias<LS, true>(ldsu + LY::W1A + blk16 * LY::N1A * 256 + 4 * lane, cut(0));
+            if constexpr (Shape<KSH>::BIAS)
+#pragma unroll
+                for (int h = 0; h < NH; ++h)
+                    put_bias<KSH, false>(ldsu + LY::WHA + (h * NB + blk16) * LY::NHA * 256 + 4 * lane, cut(1 + h));
+        }
+        float l1c = 0.0f, braw[NPL];
+#pragma unroll
+        for (int i = 0; i < NPL; ++i) {
+            const int n = lane + 64 * i, at = swz(min(n, LY::N - 1));
+            const float w = w3v[i] * pow2_above(lds[LY::BND + NH * LY::N + at]);
+            l1c += fabsf(w);
+            if (n < LY::N && wave < 3)
+                lds[LY::W3 + wave * LY::N + at] = w;
+            if constexpr (LY::HB > 0) {
+                braw[i] = bv[i] * pow2_inverse(pow2_above(lds[LY::BND + lw * LY::N + at]));
+                if (n < LY::N && wave >= 1 && wave <= NH)
+                    lds[LY::RAWB + (wave - 1) * LY::N + at] = braw[i];
             }
         }
-        // biases that start an accumulator: times wsc / (bias scale), so that
-        // the pixel's bias activation completes them
-        if (!Shape<KSH>::BIAS && NH > 0 && wave >= 1 && wave <= NH) {
-            float k = bsc[1];
+        l1c = wave_sum(l1c);
+        if (lane == 0)
+            lds[LY::L1C + wave] = l1c;
+        if (blk < tiles) {
+            const float t = tile_scale(fmaxf(max4(*reinterpret_cast<const f32x4 *>(&lds[LY::XMAX])), xfloor), inv_t);
+            sb = t * rho;
+            if (any_flag(ldsu + LY::BAD) == 0)
+                each_box_reg<LV, THT>([&](int i, int k) { boxv[i] *= ck[k] * t; });
+            store_boxes<LV, THT>(lds + LY::LAT, boxv, tid);
+            if constexpr (LY::HB > 0)
 #pragma unroll
-            for (int l = 2; l <= NH; ++l)
-                k = wave == l ? bsc[l] : k;
-#pragma unroll
-            for (int i = 0; i < NPL; ++i)
-                if (lane + 64 * i < LY::N)
-                    lds[LY::BIAS + wave * LY::N + swz(lane + 64 * i)] = bv[i] * k;
+                for (int i = 0; i < NPL; ++i)
+                    if (lane + 64 * i < LY::N && wave >= 1 && wave <= NH)
+                        lds[LY::BIAS + (wave - 1) * LY::N + swz(lane + 64 * i)] = braw[i] * t;
         }
+        __syncthreads();
     }
-    __syncthreads();
+    // a channel's least acceptable partial sum: E_c times 2^18 / 2^13 or what
+    // lies between (the header says why), by the narrowest hidden layer
+    float thr[3];
+    {
+        int n = p.widths[1];
+#pragma unroll
+        for (int l = 2; l <= NH + 1; ++l)
+            n = min(n, p.widths[l]);
+        const float above = NH == 0 || n < 32 ? 0x1p18f
+                                              : (n < 64 ? 0x1p16f : n < 96 ? 0x1p15f : n < 128 ? 0x1p14f : 0x1p13f) *
+                                                    (NH == 2 ? 0.5f : 1.0f);
+        const float err = max4(*reinterpret_cast<const f32x4 *>(&lds[LY::ERR + NH * kWaves])) * (above * 0x1p-25f);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            thr[c] = uniform(err * lds[LY::L1C + c]);
+    }
 
     const int64_t plane = (int64_t)H * W;
     // Lane group g (< 3) stores channel g.
@@ -556,24 +806,31 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
     };
 
     // the output layer on the vector ALU: partial sums over this lane's
-    // values in two chains, then a sum over the four lane groups (lane group
-    // g < 3: channel g).  (Four chains: the same error, 10 us more of 768x512
-    // x 64's 510.)
-    auto output = [&](const f32x4 (&d)[NB]) {
-        float o[3][2];
+    // values in two chains.  (Four chains: the same error, 10 us more of
+    // 768x512 x 64's 510.)  w(c, ob): channel c's weights of block ob.
+    auto output = [&](const f32x4 (&d)[NB], float (&o)[3], auto w) {
+        float a[3][2];
 #pragma unroll
         for (int ob16 = 0; ob16 < NB; ++ob16) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const f32x4 w3 = *reinterpret_cast<const f32x4 *>(&lds[LY::W3 + c * LY::N + 16 * ob16 + 4 * g]);
+                const f32x4 w3 = w(c, ob16);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (4 * ob16 + r < KSH)
-                        o[c][r & 1] = ob16 == 0 && r < 2 ? w3[r] * d[ob16][r]
-                                                         : __builtin_fmaf(w3[r], d[ob16][r], o[c][r & 1]);
+                        a[c][r & 1] = ob16 == 0 && r < 2 ? w3[r] * d[ob16][r]
+                                                         : __builtin_fmaf(w3[r], d[ob16][r], a[c][r & 1]);
             }
         }
-        return row_sum3(o[0][0] + o[0][1], o[1][0] + o[1][1], o[2][0] + o[2][1]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            o[c] = a[c][0] + a[c][1];
+    };
+    // bit i: one of the four partial sums o of column i's pixel is at least t
+    auto covered = [](float o, float t) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(fabsf(o) >= t);
+        const unsigned f = (unsigned)m | (unsigned)(m >> 32);
+        return f | f >> 16;
     };
 
     // Tiles: the workgroup's first is tile blk; the others come from its
@@ -596,25 +853,63 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
             asm volatile("" : "+s"(z), "+v"(tz));
             load_boxes<LV, THT>(v, p, b, ty0, tx0, tz, z);
             fill_taps<LV, THT>(ldsu, LY::COL, LY::ROW, LY::LAT, p, ty0, tx0, wave, lane);
-            float lsum = 0.0f;
+            float ck[LV];
 #pragma unroll
-            for (int i = 0; i < box_regs<LV, THT>(); ++i)
+            for (int k = 0; k < LV; k += 4) {
+                const f32x4 c = *reinterpret_cast<const f32x4 *>(&lds[LY::CSCALE + k]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    ck[k + i] = c[i];
+            }
+            float lsum = 0.0f, m = 0.0f;
+            each_box_reg<LV, THT>([&](int i, int k) {
                 lsum += fabsf(v[i]);
-            store_boxes<LV, THT>(lds + LY::LAT, v, tz);
+                m = fmaxf(m, fabsf(v[i]) * ck[k]);
+            });
             const bool tbad = __any(!(lsum < kRange));
-            if (lane == 0)
+            m = wave_max(m);
+            if (lane == 0) {
                 ldsu[LY::BAD + wave] = tbad;
+                lds[LY::XMAX + wave] = m;
+            }
+            __syncthreads();
+            const float tsc = tile_scale(fmaxf(max4(*reinterpret_cast<const f32x4 *>(&lds[LY::XMAX])), xfloor), inv_t);
+            if (any_flag(ldsu + LY::BAD) == 0)
+                each_box_reg<LV, THT>([&](int i, int k) { v[i] *= ck[k] * tsc; });
+            store_boxes<LV, THT>(lds + LY::LAT, v, tz);
+            sb = tsc * rho;
+            if constexpr (LY::HB > 0)
+#pragma unroll
+                for (int i = 0; i < NPL; ++i)
+                    if (lane + 64 * i < LY::N && wave >= 1 && wave <= NH) {
+                        const int at = (wave - 1) * LY::N + swz(lane + 64 * i);
+                        lds[LY::BIAS + at] = lds[LY::RAWB + at] * tsc;
+                    }
             __syncthreads();
         }
         int ticket = 0;    // the tile after this one; its latency hides behind the tile
         if (dynamic && tid == 0)
             ticket = atomicAdd(ts.ctr, 1);
-        const u32x4 f0 = *reinterpret_cast<const u32x4 *>(&ldsu[LY::BAD]);
-        const u32x4 f1 = *reinterpret_cast<const u32x4 *>(&ldsu[LY::BAD + kWaves]);
-        const unsigned bad = __builtin_amdgcn_readfirstlane(f0[0] | f0[1] | f0[2] | f0[3] | f1[0] | f1[1] | f1[2] |
-                                                            f1[3]);
+        // out of range: the boxes hold the levels as they are.  (Biases cut to
+        // -65504 sb stay below -2^16, dead, while sb is at least 1; where some
+        // are large, their lower parts count while it is at least 2^-12.)
+        const unsigned raw = any_flag(ldsu + LY::BAD);
+        const unsigned bad = raw | (steep && __builtin_amdgcn_readfirstlane(sb < 2.0f) != 0 ? 1u : 0u);
         const int rows = min(RPW, H - ty0 - RPW * wave);    // of this wavefront (<= 0: none)
+        // groups of the wavefront's rows to evaluate in binary32, a bit each
+        static_assert(RPW * TWG <= 32, "a bit per group");
+        unsigned again = 0;
         if (bad == 0) {
+            // the least partial sums, 0 where the output bias covers them (or
+            // no output of any size could tell)
+            const float th0 = uniform(fmaxf(fabsf(b3_0), 0x1p-60f) >= thr[0] * inv_t ? 0.0f : thr[0]);
+            const float th1 = uniform(fmaxf(fabsf(b3_1), 0x1p-60f) >= thr[1] * inv_t ? 0.0f : thr[1]);
+            const float th2 = uniform(fmaxf(fabsf(b3_2), 0x1p-60f) >= thr[2] * inv_t ? 0.0f : thr[2]);
+            const bool check = !(th0 + th1 + th2 == 0.0f);
+            // the bias activation's word: sb against a bias's upper part, sb
+            // 2^-kLow against its lower parts
+            const unsigned sw = __builtin_bit_cast(
+                unsigned, __builtin_convertvector((f32x2{sb, sb * (1.0f / (1 << kLow))}), f16x2));
 #pragma unroll 1
             for (int rr = 0; rr < rows; ++rr) {
                 const int yr = RPW * wave + rr;
@@ -628,29 +923,12 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                     // (A later group of a pass may lie right of the image: its
                     // taps are those of the last column, its store is skipped.)
                     asm volatile("" ::: "memory");
-                    float v1[G][LS], s[G], sc[G], inv[G];
+                    float v1[G][LS];
                     f32x4 d[G][NB];
 #pragma unroll
-                    for (int gi = 0; gi < G; ++gi) {
+                    for (int gi = 0; gi < G; ++gi)
                         sample(yr, cg + gi, v1[gi]);
-                        float m = mfloor;
-#pragma unroll
-                        for (int q = 0; q < LS; ++q)
-                            m = fmaxf(m, fabsf(v1[gi][q]));
-                        // the power of two that brings m into [2^5, 2^6), and
-                        // its inverse times the weight scales'
-                        const int e = column_max(m) & 0x7f800000;
-                        sc[gi] = __int_as_float((259 << 23) - e);
-                        inv[gi] = __int_as_float(e - (5 << 23));
-#pragma unroll
-                        for (int q = 0; q < LS; ++q)
-                            v1[gi][q] *= sc[gi];
-                        s[gi] = sc[gi] * sscale[0];
-#pragma unroll
-                        for (int o = 0; o < NB; ++o)
-                            d[gi][o] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                    }
-                    apply<LS, true, NB, G>(ldsu + LY::W1A + 4 * lane, v1, s, d);
+                    apply<LS, true, NB, G>(ldsu + LY::W1A + 4 * lane, lds, sw, v1, d);
 
                     // hidden layers: the outputs are the next layer's inputs,
                     // scaled as they stand
@@ -658,108 +936,135 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                     for (int h = 0; h < NH; ++h) {
                         float v[G][KSH];
 #pragma unroll
-                        for (int gi = 0; gi < G; ++gi) {
+                        for (int gi = 0; gi < G; ++gi)
 #pragma unroll
-                            for (int q = 0; q < KSH; ++q) {
+                            for (int q = 0; q < KSH; ++q)
                                 v[gi][q] = relu(d[gi][q >> 2][q & 3]);
-                                if (h > 0)
-                                    v[gi][q] *= 0x1p-22f;
-                            }
-                            s[gi] = sc[gi] * sscale[1 + h];
-                        }
-#pragma unroll
-                        for (int o = 0; o < NB; ++o) {
-                            if constexpr (Shape<KSH>::BIAS) {
-#pragma unroll
-                                for (int gi = 0; gi < G; ++gi)
-                                    d[gi][o] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                            } else {
-                                const f32x4 bias =
-                                    *reinterpret_cast<const f32x4 *>(&lds[LY::BIAS + (1 + h) * LY::N + 16 * o + 4 * g]);
-#pragma unroll
-                                for (int gi = 0; gi < G; ++gi)
-#pragma unroll
-                                    for (int r = 0; r < 4; ++r)
-                                        if (4 * o + r < KSH)
-                                            d[gi][o][r] = bias[r] * s[gi];
-                            }
-                        }
-                        apply<KSH, false, NB, G>(ldsu + LY::WHA + h * NB * LY::NHA * 256 + 4 * lane, v, s, d);
+                        apply<KSH, false, NB, G>(ldsu + LY::WHA + h * NB * LY::NHA * 256 + 4 * lane,
+                                                 lds + LY::BIAS + h * LY::N + 4 * g, sw, v, d);
                     }
+                    float o[G][3];
 #pragma unroll
                     for (int gi = 0; gi < G; ++gi) {
 #pragma unroll
                         for (int q = 0; q < KSH; ++q)
                             d[gi][q >> 2][q & 3] = relu(d[gi][q >> 2][q & 3]);
-                        const float o = __builtin_fmaf(output(d[gi]), inv[gi] * unscale, ob);
+                        output(d[gi], o[gi], [&](int c, int o16) {
+                            return *reinterpret_cast<const f32x4 *>(&lds[LY::W3 + c * LY::N + 16 * o16 + 4 * g]);
+                        });
+                    }
+                    if (check) {
+#pragma unroll
+                        for (int gi = 0; gi < G; ++gi) {
+                            const unsigned ok = covered(o[gi][0], th0) & covered(o[gi][1], th1) & covered(o[gi][2], th2);
+                            again |= ((ok & 0xffff) != 0xffff ? 1u : 0u) << (rr * TWG + cg + gi);
+                        }
+                    }
+#pragma unroll
+                    for (int gi = 0; gi < G; ++gi) {
+                        const float v = __builtin_fmaf(row_sum3(o[gi][0], o[gi][1], o[gi][2]), inv_t, ob);
                         if (g < 3 && tx0 + 16 * (cg + gi) + col < W)
-                            store_out(p, orow + 16 * (cg + gi), o);
+                            store_out(p, orow + 16 * (cg + gi), v);
                     }
                 }
             }
-        } else {
+        } else if (rows > 0) {
+            again = ~0u >> (32 - rows * TWG);
+        }
+        if (again != 0) {
             // fp32 matrix instructions (v_mfma_f32_16x16x4_f32: A[i][g],
             // B[g][i] from lane l, the same D), the products in binary32 as
-            // they stand, the weights and biases from global memory
-            auto weight = [&](int l, int n, int k) {
-                const LayerParams lp = layer_params(p, l, b);
-                const bool ok = n < p.widths[l + 1] && k < p.widths[l];
-                const float w = lp.weight(ok ? n * p.widths[l] + k : 0);
-                return ok ? w : 0.0f;
+            // they stand, the weights and biases from global memory through
+            // raw buffers (0 past the array's end; inputs past a layer's: an
+            // offset past it).  The levels' scales come off exactly.
+            int z = 0;    // (opaque, so that no layer's geometry is kept over the other tiles)
+            asm volatile("" : "+s"(z));
+            float back[LS];
+#pragma unroll
+            for (int q = 0; q < LS; ++q)
+                back[q] = raw ? 1.0f : level_unscale(lds[LY::CSCALE + 4 * q + g]) * inv_t;
+            auto ld = [](__amdgpu_buffer_rsrc_t r, unsigned at) {
+                return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
             };
-            auto bias = [&](int l, int n) {
-                const LayerParams lp = layer_params(p, l, b);
-                const bool ok = n < p.widths[l + 1];
-                const float v = lp.b[ok ? n : 0];
-                return ok ? v : 0.0f;
-            };
-#pragma unroll 1
-            for (int i = 0; i < rows * TWG; ++i) {
-                const int yr = RPW * wave + i / TWG, cg = i % TWG;
+            auto layer = [&](int l, auto &d, auto in, int kq) {
+                const LayerParams lp = layer_params(p, l + z, b);
+                const unsigned fin = p.widths[l + z], fout = p.widths[l + z + 1];
+                const auto wb = raw_buffer(lp.w, fin * fout * 4), bb = raw_buffer(lp.b, fout * 4);
                 // (opaque, so that no operand or its address is kept over the
                 // tiles that do not come here)
-                int n0 = row_neuron(col), k0 = g;
+                unsigned n0 = row_neuron(col), k0 = g;
                 asm volatile("" : "+v"(n0), "+v"(k0)::"memory");
-                float u[LS];
-                sample(yr, cg, u);
-                f32x4 d[NB];
 #pragma unroll
                 for (int o = 0; o < NB; ++o)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        d[o][r] = bias(0, 16 * o + 4 * r + k0);
+                    for (int r = 0; r < 4; ++r) {
+                        const float v = ld(bb, (16 * o + 4 * r + k0) * 4);
 #pragma unroll
-                for (int q = 0; q < LS; ++q)
+                        for (int gi = 0; gi < G; ++gi)
+                            d[gi][o][r] = v;
+                    }
 #pragma unroll
-                    for (int o = 0; o < NB; ++o)
-                        d[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(weight(0, 16 * o + n0, 4 * q + k0),
-                                                                    4 * q + k0 < L ? u[q] : 0.0f, d[o], 0, 0, 0);
+                for (int q = 0; q < kq; ++q) {
+                    asm volatile("" : "+v"(n0), "+v"(k0)::"memory");
+                    const unsigned k = 4 * q + k0, at = k < fin ? (n0 * fin + k) * 4 : 0x40000000u;
 #pragma unroll
-                for (int h = 0; h < NH; ++h) {
-                    float v[KSH];
+                    for (int o = 0; o < NB; ++o) {
+                        const float w = ld(wb, at + 16 * o * fin * 4);
 #pragma unroll
-                    for (int q = 0; q < KSH; ++q)
-                        v[q] = relu(d[q >> 2][q & 3]);
-#pragma unroll
-                    for (int o = 0; o < NB; ++o)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            d[o][r] = bias(1 + h, 16 * o + 4 * r + k0);
-#pragma unroll
-                    for (int q = 0; q < KSH; ++q) {
-                        asm volatile("" : "+v"(n0), "+v"(k0)::"memory");
-#pragma unroll
-                        for (int o = 0; o < NB; ++o)
-                            d[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(weight(1 + h, 16 * o + n0, 4 * q + k0), v[q],
-                                                                        d[o], 0, 0, 0);
+                        for (int gi = 0; gi < G; ++gi)
+                            d[gi][o] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, in(gi, q), d[gi][o], 0, 0, 0);
                     }
                 }
+            };
+#pragma unroll 1
+            for (int i = 0; i < rows * TWG; i += G) {
+                const unsigned mine = again >> i & ((1u << G) - 1);
+                if (mine == 0)
+                    continue;
+                const int yr = RPW * wave + i / TWG, cg = i % TWG;
+                float u[G][LS];
+                f32x4 d[G][NB];
 #pragma unroll
-                for (int q = 0; q < KSH; ++q)
-                    d[q >> 2][q & 3] = relu(d[q >> 2][q & 3]);
-                const float o = output(d) + ob;
-                if (g < 3 && tx0 + 16 * cg + col < W)
-                    store_out(p, obase + (uint32_t)((ty0 + yr) * W + tx0 + 16 * cg + col), o);
+                for (int gi = 0; gi < G; ++gi) {
+                    sample(yr, cg + gi, u[gi]);
+#pragma unroll
+                    for (int q = 0; q < LS; ++q)
+                        u[gi][q] = 4 * q + g < L ? u[gi][q] * back[q] : 0.0f;
+                }
+                layer(0, d, [&](int gi, int q) { return u[gi][q]; }, LS);
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    float v[G][KSH];
+#pragma unroll
+                    for (int gi = 0; gi < G; ++gi)
+#pragma unroll
+                        for (int q = 0; q < KSH; ++q)
+                            v[gi][q] = relu(d[gi][q >> 2][q & 3]);
+                    layer(1 + h, d, [&](int gi, int q) { return v[gi][q]; }, KSH);
+                }
+                const unsigned NL = p.widths[NH + 1 + z];
+                const auto w3b = raw_buffer(layer_params(p, NH + 1 + z, b).w, 3 * NL * 4);
+#pragma unroll
+                for (int gi = 0; gi < G; ++gi) {
+#pragma unroll
+                    for (int q = 0; q < KSH; ++q)
+                        d[gi][q >> 2][q & 3] = relu(d[gi][q >> 2][q & 3]);
+                    float o[3];
+                    output(d[gi], o, [&](int c, int o16) {
+                        f32x4 w;
+                        unsigned n0 = g;
+                        asm volatile("" : "+v"(n0)::"memory");
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const unsigned n = 16 * o16 + 4 * r + n0;
+                            w[r] = ld(w3b, n < NL ? (c * NL + n) * 4 : 0x40000000u);
+                        }
+                        return w;
+                    });
+                    const float v = row_sum3(o[0], o[1], o[2]) + ob;
+                    if ((mine >> gi & 1) && g < 3 && tx0 + 16 * (cg + gi) + col < W)
+                        store_out(p, obase + (uint32_t)((ty0 + yr) * W + tx0 + 16 * (cg + gi) + col), v);
+                }
             }
         }
         if (!dynamic)
@@ -834,30 +1139,34 @@ hipError_t launch_nh(const DecodeParams &p, hipStream_t s, int num_cus)
     return hipErrorInvalidValue;
 }
 
-// Nets 65 to 128 wide: six or eight blocks, whose operands leave room for one
-// or two workgroups in a CU's LDS (1 to 2 wavefronts per SIMD), where one
-// group of pixels a pass keeps the registers below 256.  The vector family,
-// which ran these nets before, evaluates a pixel per lane at 13 TFLOP/s: 768x512,
-// 8 -> 96 -> 96 -> 3: 606 -> 39 us, 8 -> 128 -> 128 -> 128 -> 3: 1777 -> 105,
-// 4 -> 100 -> 3: 86 -> 16; 64x64, 12 -> 128 -> 128 -> 3: 156 -> 28.
-// (wide_fits: the operands of a 128-wide net with two hidden matrices and
-// more than 8 levels do not fit the LDS.)
+// Nets 65 to 128 wide: six or eight blocks, one group of pixels a pass.  With a
+// hidden matrix their operands leave room for one or two workgroups in a CU's
+// LDS (1 or 2 wavefronts per SIMD), without one 20 to 43 KB for two or three;
+// the eight-block instances of two hidden matrices take all 256 VGPRs and some
+// AGPRs.  The vector family, which evaluates a pixel per lane at 13 TFLOP/s,
+// against these: 768x512, 8 -> 96 -> 96 -> 3: 604 -> 39 us, 8 -> 128 -> 128 -> 128
+// -> 3: 1772 -> 103, 4 -> 100 -> 3: 86 -> 16; 64x64, 12 -> 128 -> 128 -> 3: 156 -> 32.
+// (wide_fits: the operands of a 128-wide net with two hidden matrices do not
+// fit the LDS with more than 8 levels, nor with 16-row tiles from 5 levels on.)
 constexpr int kWideLds = 160 * 1024;
-template <int NB, int NH, int LS>
-constexpr bool wide_fits = Layout<NB, NH, LS, 4 * NB, 4 * kWaves>::SIZE * 4 + 64 <= kWideLds;
+template <int NB, int NH, int LS, int RPW>
+constexpr bool wide_fits = Layout<NB, NH, LS, 4 * NB, RPW * kWaves>::SIZE * 4 + 64 <= kWideLds;
 
 template <int NB, int NH, int LS>
 hipError_t launch_wide_one(const DecodeParams &p, hipStream_t s, int num_cus)
 {
-    if constexpr (wide_fits<NB, NH, LS>) {
+    if constexpr (wide_fits<NB, NH, LS, 2>) {
         const int tiles_x = (p.W + TW - 1) / TW;
         const int tiles8 = tiles_x * ((p.H + TH - 1) / TH);
-        const int tiles16 = tiles_x * ((p.H + 4 * kWaves - 1) / (4 * kWaves));
-        static int occ8 = 0, occ16 = 0;
+        static int occ8 = 0;
         const int bpi8 = blocks_per_image(k_mfma_f16x3<NB, NH, LS, 4 * NB, 2>, p, num_cus, tiles8, occ8);
-        const int bpi16 = blocks_per_image(k_mfma_f16x3<NB, NH, LS, 4 * NB, 4>, p, num_cus, tiles16, occ16);
-        if (occ16 >= occ8 && tiles16 >= 2 * bpi16)
-            return launch_rows<NB, NH, LS, 4 * NB, 4>(p, s, tiles_x, tiles16, bpi16);
+        if constexpr (wide_fits<NB, NH, LS, 4>) {
+            const int tiles16 = tiles_x * ((p.H + 4 * kWaves - 1) / (4 * kWaves));
+            static int occ16 = 0;
+            const int bpi16 = blocks_per_image(k_mfma_f16x3<NB, NH, LS, 4 * NB, 4>, p, num_cus, tiles16, occ16);
+            if (occ16 >= occ8 && tiles16 >= 2 * bpi16)
+                return launch_rows<NB, NH, LS, 4 * NB, 4>(p, s, tiles_x, tiles16, bpi16);
+        }
         return launch_rows<NB, NH, LS, 4 * NB, 2>(p, s, tiles_x, tiles8, bpi8);
     } else {
         return hipErrorInvalidValue;
