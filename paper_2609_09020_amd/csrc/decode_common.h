@@ -234,6 +234,15 @@ __device__ __forceinline__ uint32_t texel(int r, int wk, int c)
     return __umul24((uint32_t)r, (uint32_t)wk) + (uint32_t)c;
 }
 
+// Index of pixel (y, x) in an image W wide, unsigned: the lanes of a group that
+// ends right of the image go up to 62 past its last pixel, which is past 2^31 - 1
+// in the largest images.
+__host__ __device__ constexpr uint32_t pixel_index(int y, int W, int x)
+{
+    return (uint32_t)y * (uint32_t)W + (uint32_t)x;
+}
+static_assert(pixel_index(330, 6487866, 6487865 + 62) == (1u << 31) + 59, "331 x 6487866, within the limits");
+
 // Row of tile t in a grid tiles_x tiles wide, t / tiles_x, as the high half of
 // t m for the host's m = ceil(2^32 / tiles_x) = (2^32 + e) / tiles_x, 0 <= e <
 // tiles_x: t m / 2^32 exceeds t / tiles_x by t e / (tiles_x 2^32), which stays

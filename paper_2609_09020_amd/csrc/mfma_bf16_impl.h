@@ -239,7 +239,7 @@ void k_mfma_bf16(DecodeParams p, int blocks_per_image, int tiles_x, int tiles, u
 #pragma unroll 1
         for (int rr = 0; rr < rows; ++rr) {
             const int yr = RPW * wave + rr;
-            const int64_t orow = obase + (uint32_t)((ty0 + yr) * W + tx0 + col);   // < H W + 64 <= 2^31 + 63
+            const int64_t orow = obase + pixel_index(ty0 + yr, W, tx0 + col);
 
 #pragma unroll
             for (int cg = 0; cg < TWG; cg += G) {

@@ -913,7 +913,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
 #pragma unroll 1
             for (int rr = 0; rr < rows; ++rr) {
                 const int yr = RPW * wave + rr;
-                const int64_t orow = obase + (uint32_t)((ty0 + yr) * W + tx0 + col);   // < H W + 64 <= 2^31 + 63
+                const int64_t orow = obase + pixel_index(ty0 + yr, W, tx0 + col);
 #pragma unroll
                 for (int cg = 0; cg < TWG; cg += G) {
                     if (tx0 + 16 * cg >= W)
@@ -1063,7 +1063,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                     });
                     const float v = row_sum3(o[0], o[1], o[2]) + ob;
                     if ((mine >> gi & 1) && g < 3 && tx0 + 16 * (cg + gi) + col < W)
-                        store_out(p, obase + (uint32_t)((ty0 + yr) * W + tx0 + 16 * (cg + gi) + col), v);
+                        store_out(p, obase + pixel_index(ty0 + yr, W, tx0 + 16 * (cg + gi) + col), v);
                 }
             }
         }

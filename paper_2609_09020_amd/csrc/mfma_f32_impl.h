@@ -291,7 +291,7 @@ void k_mfma_f32(DecodeParams p, int blocks_per_image, int tiles_x, int tiles, ui
 #pragma unroll
             for (int s = 0; s < LS; ++s)
                 lane_level_row(lv[s], y, roff[s], rly[s]);
-            const int64_t orow = obase + (uint32_t)(y * W + tx0 + col);   // < H W + 64 <= 2^31 + 63
+            const int64_t orow = obase + pixel_index(y, W, tx0 + col);
 
             // 8-row tiles (small launches, mostly one tile per workgroup)
             // evaluate two 16-pixel groups per pass: their matrix chains
