@@ -416,11 +416,13 @@ class Decoder:
 
     def run(self, latents, weights, biases, out=None, batch: Optional[int] = None, stream=None):
         import torch
+        if len(latents) != self.levels:
+            raise ValueError(f"expected {self.levels} latent levels, got {len(latents)}")
         n = latents[0].shape[0] if batch is None else int(batch)
         di = latents[0].get_device()
         f32 = torch.float32
         _, shapes, oshape = self._shapes(n)
-        if out is None or di < 0 or len(latents) != self.levels or out.shape != oshape or \
+        if out is None or di < 0 or out.shape != oshape or \
                 out.get_device() != di or not out.is_contiguous() or \
                 out.dtype is not (torch.uint8 if self.out_dtype == "u8" else f32) or \
                 biases.dtype is not f32 or not biases.is_contiguous() or biases.get_device() != di or \
@@ -446,8 +448,6 @@ class Decoder:
     def _run_checked(self, latents, weights, biases, out, batch, stream):
         import torch
         batch = latents[0].shape[0] if batch is None else int(batch)
-        if len(latents) != self.levels:
-            raise ValueError(f"expected {self.levels} latent levels, got {len(latents)}")
         dev = latents[0].device
         if dev.type != "cuda":
             raise ValueError("latents must be device tensors")
