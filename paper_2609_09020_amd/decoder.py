@@ -358,9 +358,11 @@ def pic_huff_destroy(handle: int) -> None:
 # go through the checks that word the errors only where that pass fails.
 
 
-def _raw_stream(device_index: int) -> int:
+def _raw_stream(device_index: Optional[int]) -> int:
     """torch's current stream on that device, as the hipStream_t."""
     import torch
+    if device_index is None:
+        raise ValueError("expected tensors on a GPU")
     get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if get is not None:
         return get(device_index)

@@ -69,3 +69,11 @@ def test_run_reaches_the_library_and_refuses_wrong_level_counts():
         with pytest.raises(ValueError, match="latent levels"):
             d.run(latents, _Tensor((20,)), _Tensor((7,)), out=out, batch=2, stream=0)
     assert len(d._lib.calls) == 1
+
+
+def test_layers_on_the_host_are_refused():
+    d = _synthesis()
+    t = [torch.zeros(1, 8, 8), torch.zeros(1, 4, 4)]
+    w, b = [torch.zeros(4, 2), torch.zeros(3, 4)], [torch.zeros(4), torch.zeros(3)]
+    with pytest.raises(ValueError):
+        d.run_layers(t, w, b, out=torch.zeros(1, 3, 8, 8))
