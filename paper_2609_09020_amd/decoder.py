@@ -403,10 +403,12 @@ class Decoder:
         return (-(-self.height // f), -(-self.width // f))
 
     def _shapes(self, batch: int):
-        if self._shapes_of[0] != batch:
-            self._shapes_of = (batch, [(batch,) + self.level_shape(k) for k in range(self.levels)],
-                               (batch, 3, self.height, self.width))
-        return self._shapes_of
+        # (one read: another thread may put its own batch's there meanwhile)
+        kept = self._shapes_of
+        if kept[0] != batch:
+            kept = self._shapes_of = (batch, [(batch,) + self.level_shape(k) for k in range(self.levels)],
+                                      (batch, 3, self.height, self.width))
+        return kept
 
     def info(self) -> dict:
         return pic_decode_query(self.handle)
@@ -580,11 +582,12 @@ class ZprDecoder:
         i32, f32 = torch.int32, torch.float32
         if latents is not None and status is not None and len(latents) == self.levels and 0 <= n <= self.max_batch:
             di = symbols.get_device()
-            if self._shapes_of[0] != n:
-                self._shapes_of = (n, [(n,) + self.level_shape(k) for k in range(self.levels)])
+            kept = self._shapes_of
+            if kept[0] != n:
+                kept = self._shapes_of = (n, [(n,) + self.level_shape(k) for k in range(self.levels)])
             if di >= 0 and symbols.dtype is i32 and symbols.dim() == 1 and symbols.is_contiguous() and \
                     status.dtype is i32 and status.get_device() == di and status.is_contiguous():
-                ptrs = [t.data_ptr() for t, shape in zip(latents, self._shapes_of[1])
+                ptrs = [t.data_ptr() for t, shape in zip(latents, kept[1])
                         if t.shape == shape and t.dtype is f32 and t.get_device() == di and t.is_contiguous()]
                 if len(ptrs) == self.levels:
                     st = self._lib.pic_zpr_decode(self.handle, n, symbols.data_ptr(), symbols.numel(), int(eob),

@@ -42,6 +42,20 @@ class _Library:
     pic_zpr_decode = pic_decode_run
 
 
+class _Shared:
+    """The kept shapes as a thread sees them while another one, of batch 1, works:
+    whatever is stored, the next read may find the other's."""
+
+    def __set_name__(self, owner, name):
+        self.name = "_" + name
+
+    def __get__(self, obj, owner):
+        return getattr(obj, self.name)
+
+    def __set__(self, obj, value):
+        setattr(obj, self.name, obj.other())
+
+
 def _decoder(cls, **kw):
     d = object.__new__(cls)
     d.height, d.width, d.levels, d.max_batch, d.handle = 8, 8, 2, 4, None
@@ -77,3 +91,25 @@ def test_layers_on_the_host_are_refused():
     w, b = [torch.zeros(4, 2), torch.zeros(3, 4)], [torch.zeros(4), torch.zeros(3)]
     with pytest.raises(ValueError):
         d.run_layers(t, w, b, out=torch.zeros(1, 3, 8, 8))
+
+
+def test_shapes_of_another_threads_batch_do_not_pass_too_small_tensors():
+    class D(Decoder):
+        _shapes_of = _Shared()
+
+        def other(self):
+            return (1, [(1, 8, 8), (1, 4, 4)], (1, 3, 8, 8))
+
+    class Z(ZprDecoder):
+        _shapes_of = _Shared()
+
+        def other(self):
+            return (1, [(1, 8, 8), (1, 4, 4)])
+
+    d = _synthesis(D)
+    with pytest.raises(ValueError):
+        d.run(_levels(1), _Tensor((20,)), _Tensor((7,)), out=_Tensor((1, 3, 8, 8)), batch=4, stream=0)
+    z = _decoder(Z, _shapes_of=(None, None))
+    with pytest.raises(ValueError):
+        z.decode(_Tensor((10,), torch.int32), 77, batch=4, latents=_levels(1), status=_Tensor((1,), torch.int32), stream=0)
+    assert not d._lib.calls and not z._lib.calls
