@@ -977,6 +977,11 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
             // they stand, the weights and biases from global memory through
             // raw buffers (0 past the array's end; inputs past a layer's: an
             // offset past it).  The levels' scales come off exactly.
+            // (Latency of the weights binds it: with four K steps' in flight and G
+            // groups per read, every tile of 3840x2160, 8 -> 64 -> 64 -> 3, takes
+            // 2080 us, of which one step and one group took 3890, and the fp32
+            // family 616; one tile of 768x512, 7 -> 40 -> 40 -> 3, adds 5 us to 18,
+            // where it added 33.)
             int z = 0;    // (opaque, so that no layer's geometry is kept over the other tiles)
             asm volatile("" : "+s"(z));
             float back[LS];
@@ -986,6 +991,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
             auto ld = [](__amdgpu_buffer_rsrc_t r, unsigned at) {
                 return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
             };
+            constexpr int kAhead = 4;    // K steps whose weights are in flight together
             auto layer = [&](int l, auto &d, auto in, int kq) {
                 const LayerParams lp = layer_params(p, l + z, b);
                 const unsigned fin = p.widths[l + z], fout = p.widths[l + z + 1];
@@ -1004,16 +1010,23 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                             d[gi][o][r] = v;
                     }
 #pragma unroll
-                for (int q = 0; q < kq; ++q) {
+                for (int q0 = 0; q0 < kq; q0 += kAhead) {
                     asm volatile("" : "+v"(n0), "+v"(k0)::"memory");
-                    const unsigned k = 4 * q + k0, at = k < fin ? (n0 * fin + k) * 4 : 0x40000000u;
+                    float w[kAhead][NB];
 #pragma unroll
-                    for (int o = 0; o < NB; ++o) {
-                        const float w = ld(wb, at + 16 * o * fin * 4);
+                    for (int q = q0; q < kq && q < q0 + kAhead; ++q) {
+                        const unsigned k = 4 * q + k0, at = k < fin ? (n0 * fin + k) * 4 : 0x40000000u;
 #pragma unroll
-                        for (int gi = 0; gi < G; ++gi)
-                            d[gi][o] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, in(gi, q), d[gi][o], 0, 0, 0);
+                        for (int o = 0; o < NB; ++o)
+                            w[q - q0][o] = ld(wb, at + 16 * o * fin * 4);
                     }
+#pragma unroll
+                    for (int q = q0; q < kq && q < q0 + kAhead; ++q)
+#pragma unroll
+                        for (int o = 0; o < NB; ++o)
+#pragma unroll
+                            for (int gi = 0; gi < G; ++gi)
+                                d[gi][o] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[q - q0][o], in(gi, q), d[gi][o], 0, 0, 0);
                 }
             };
 #pragma unroll 1
@@ -1050,10 +1063,11 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                     for (int q = 0; q < KSH; ++q)
                         d[gi][q >> 2][q & 3] = relu(d[gi][q >> 2][q & 3]);
                     float o[3];
+                    unsigned n0 = g;
                     output(d[gi], o, [&](int c, int o16) {
                         f32x4 w;
-                        unsigned n0 = g;
-                        asm volatile("" : "+v"(n0)::"memory");
+                        if (c == 0)    // (a block's weights in flight at a time)
+                            asm volatile("" : "+v"(n0)::"memory");
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const unsigned n = 16 * o16 + 4 * r + n0;
