@@ -50,12 +50,13 @@
 // 1/680, 1/1250 (one, 40, 64, 96, 128 wide) or 1/240, 1/740, 1/1200, 1/2800 (two;
 // largest error over 8192 pixels, nets drawn at random, a texel that raises X so
 // that little else is seen).  A 16-pixel group counts only if each of its pixels
-// has, for each channel, an output bias or one of its four partial sums above E_c
-// times 2^23 times that, about: then what is lost stays below 1e-7 of it.  Other
-// groups are evaluated again by the fp32 matrix instructions.  Nets of any common
-// distribution pass by a factor of 4 to 300 (whatever the scales of their levels,
-// neurons and biases); tiles with a texel 2^12 times larger than the rest, or
-// nets whose sums cancel, do not.
+// has, for each channel, an output bias or one of its four partial sums of at
+// least E_c times 2^18 (no hidden matrix, or a layer under 32 wide), 2^16 (under
+// 64), 2^15 (under 96), 2^14 (under 128) or 2^13, half of that with two: what is
+// lost in fact is then about 1e-7 of it.  Other groups are evaluated again by the
+// fp32 matrix instructions.  Nets of any common distribution pass by a factor of
+// 4 to 300, whatever the scales of their levels, neurons and biases; tiles with a
+// texel 2^12 times larger than the rest, or nets whose sums cancel, do not.
 //
 // Range.  A workgroup with a weight or bias of 2^24 or more or B_n of 2^90, a
 // tile with a level of 2^24 or more (NaN and infinities included), and one whose
@@ -769,8 +770,8 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
         }
         __syncthreads();
     }
-    // a channel's least acceptable partial sum: E_c times 2^18 / 2^13 or what
-    // lies between (the header says why), by the narrowest hidden layer
+    // a channel's least acceptable partial sum: E_c times 2^18 to 2^12 (the
+    // header says why), by the narrowest hidden layer
     float thr[3];
     {
         int n = p.widths[1];
@@ -826,11 +827,10 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
         for (int c = 0; c < 3; ++c)
             o[c] = a[c][0] + a[c][1];
     };
-    // bit i: one of the four partial sums o of column i's pixel is at least t
-    auto covered = [](float o, float t) {
-        const uint64_t m = __builtin_amdgcn_ballot_w64(fabsf(o) >= t);
+    // bit i (of 16): whether a lane of column i is set in m
+    auto columns = [](uint64_t m) {
         const unsigned f = (unsigned)m | (unsigned)(m >> 32);
-        return f | f >> 16;
+        return (f | f >> 16) & 0xffff;
     };
 
     // Tiles: the workgroup's first is tile blk; the others come from its
@@ -954,11 +954,23 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                         });
                     }
                     if (check) {
+                        // lanes whose partial sums reach each channel's least; a
+                        // pixel with a lane that reaches all three needs no more
+                        uint64_t m[G][3];
+                        unsigned quick = 0xffff;
 #pragma unroll
                         for (int gi = 0; gi < G; ++gi) {
-                            const unsigned ok = covered(o[gi][0], th0) & covered(o[gi][1], th1) & covered(o[gi][2], th2);
-                            again |= ((ok & 0xffff) != 0xffff ? 1u : 0u) << (rr * TWG + cg + gi);
+                            m[gi][0] = __builtin_amdgcn_ballot_w64(fabsf(o[gi][0]) >= th0);
+                            m[gi][1] = __builtin_amdgcn_ballot_w64(fabsf(o[gi][1]) >= th1);
+                            m[gi][2] = __builtin_amdgcn_ballot_w64(fabsf(o[gi][2]) >= th2);
+                            quick &= columns(m[gi][0] & m[gi][1] & m[gi][2]);
                         }
+                        if (quick != 0xffff)
+#pragma unroll
+                            for (int gi = 0; gi < G; ++gi) {
+                                const unsigned ok = columns(m[gi][0]) & columns(m[gi][1]) & columns(m[gi][2]);
+                                again |= (ok != 0xffff ? 1u : 0u) << (rr * TWG + cg + gi);
+                            }
                     }
 #pragma unroll
                     for (int gi = 0; gi < G; ++gi) {
