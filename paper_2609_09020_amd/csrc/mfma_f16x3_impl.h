@@ -46,17 +46,19 @@
 // preparation measures for a weight.  Carried through the layers (each row's sum
 // of |weights| times what its inputs may be off), that bounds the outputs' error
 // in the last sums, E_c, in the worst case.  What is lost in fact, by roundings
-// that do not all point one way, is 1/40 of it (no hidden matrix), 1/180, 1/430,
-// 1/680, 1/1250 (one, 40, 64, 96, 128 wide) or 1/240, 1/740, 1/1200, 1/2800 (two;
-// largest error over 8192 pixels, nets drawn at random, a texel that raises X so
-// that little else is seen).  A 16-pixel group counts only if each of its pixels
-// has, for each channel, an output bias or one of its four partial sums of at
-// least E_c times 2^18 (no hidden matrix, or a layer under 32 wide), 2^16 (under
-// 64), 2^15 (under 96), 2^14 (under 128) or 2^13, half of that with two: what is
-// lost in fact is then about 1e-7 of it.  Other groups are evaluated again by the
-// fp32 matrix instructions.  Nets of any common distribution pass by a factor of
-// 4 to 300, whatever the scales of their levels, neurons and biases; tiles with a
-// texel 2^12 times larger than the rest, or nets whose sums cancel, do not.
+// that do not all point one way, is 1/40 of it (no hidden matrix), 1/25, 1/180,
+// 1/430, 1/680, 1/1250 (one, 16, 40, 64, 96, 128 wide) or 1/65, 1/240, 1/740,
+// 1/1200, 1/2800 (two; largest error over 8192 pixels, nets drawn at random, a
+// texel that raises X so that little else is seen).  A 16-pixel group counts only
+// if each of its pixels has, for each channel, an output bias or one of its four
+// partial sums of at least E_c times 2^16 (no hidden matrix, or a layer under 32
+// wide), 2^14 (under 64), 2^13 (under 96), 2^12 (under 128) or 2^11, half of that
+// with two: what is lost in fact is then at most about 4e-7 of it, where binary32
+// sums are off by 3e-7 (rms) to 2e-6 of it.  Other groups are evaluated again by
+// the fp32 matrix instructions.  Nets of any common distribution pass by a factor
+// of 10 to 1000, whatever the scales of their levels, neurons and biases; tiles
+// with a texel 2^14 times larger than the rest, nets whose sums cancel and pixels
+// that no neuron is active at do not.
 //
 // Range.  A workgroup with a weight or bias of 2^24 or more or B_n of 2^90, a
 // tile with a level of 2^24 or more (NaN and infinities included), and one whose
@@ -770,7 +772,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
         }
         __syncthreads();
     }
-    // a channel's least acceptable partial sum: E_c times 2^18 to 2^12 (the
+    // a channel's least acceptable partial sum: E_c times 2^16 to 2^10 (the
     // header says why), by the narrowest hidden layer
     float thr[3];
     {
@@ -778,9 +780,8 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
 #pragma unroll
         for (int l = 2; l <= NH + 1; ++l)
             n = min(n, p.widths[l]);
-        const float above = NH == 0 || n < 32 ? 0x1p18f
-                                              : (n < 64 ? 0x1p16f : n < 96 ? 0x1p15f : n < 128 ? 0x1p14f : 0x1p13f) *
-                                                    (NH == 2 ? 0.5f : 1.0f);
+        const float above = (NH == 0 || n < 32 ? 0x1p16f : n < 64 ? 0x1p14f : n < 96 ? 0x1p13f : n < 128 ? 0x1p12f : 0x1p11f) *
+                            (NH == 2 ? 0.5f : 1.0f);
         const float err = max4(*reinterpret_cast<const f32x4 *>(&lds[LY::ERR + NH * kWaves])) * (above * 0x1p-25f);
 #pragma unroll
         for (int c = 0; c < 3; ++c)
