@@ -85,14 +85,14 @@
 // What binds it (768x512 x 64, 7 -> 40 -> 40 -> 3): vector issue and, with it,
 // the chip's power; past 48 wide the LDS too (3840x2160, 8 -> 64 -> 64 -> 3:
 // 53 reads a pass, mostly of 16 bytes a lane; eight more, for bias rows, cost
-// 25 us of 270).  A 16-pixel group takes 132 vector instructions (prologue and
+// 25 us of 270).  A 16-pixel group takes 130 vector instructions (prologue and
 // tile set-up included) and 18 matrix ones; each matrix instruction keeps
-// vector ones from issuing for 8 of its 16 cycles.  768x512 x 64 477 to 490 us,
-// 2047x1365 (48 wide) 74, 3840x2160 265, one 768x512 image 15.4, of which the
-// preparation of the neurons' scales, about 300 vector instructions a wavefront
-// and two barriers, is 1.  (With one scale a layer, and one per pixel for the
-// levels, the same: 477 to 490, 74, 262, 14.6; but values 2^8 below their layer's
-// largest lost bits.)  The first version, per-layer scales from each pixel's
+// vector ones from issuing for 8 of its 16 cycles.  768x512 x 64 470 to 485 us,
+// 2047x1365 (48 wide) 74, 3840x2160 256 to 274, one 768x512 image 15.5, of which
+// the preparation of the neurons' scales, about 300 vector instructions a
+// wavefront and two barriers, is 0.9.  (With one scale a layer, and one per pixel
+// for the levels, on the same cards: 477 to 492, 75, 258 to 268, 14.6; but values
+// 2^8 below their layer's largest lost bits.)  The first version, per-layer scales from each pixel's
 // activations, remainders by v_fma_mixlo/hi_f16, which issue at half rate, the
 // biases and inverse scales applied per value, four chains in the output layer:
 // 189 vector instructions, 664, 103, 334, 17.6 us.
