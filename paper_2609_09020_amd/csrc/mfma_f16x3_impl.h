@@ -39,26 +39,26 @@
 // below), or starts the accumulators, binary32, where the operands have no slot.
 // A bias that a level of magnitude 1 cannot reach (a neuron of no weights but a
 // bias) counts in B_n as if one could; X is at least 8 times the largest b_n /
-// r_n so counted, so biases add at most 1/4 to a layer's bound.
+// r_n so counted, so biases add at most 1/8 to a layer's bound.
 //
 // What is left.  A part loses bits where a value lies 2^13 or more below the
 // bound it was scaled by: up to 2^-25 for an activation, a residue that the
 // preparation measures for a weight.  Carried through the layers (each row's sum
 // of |weights| times what its inputs may be off), that bounds the outputs' error
 // in the last sums, E_c, in the worst case.  What is lost in fact, by roundings
-// that do not all point one way, is 1/40 of it (no hidden matrix), 1/25, 1/180,
-// 1/430, 1/680, 1/1250 (one, 16, 40, 64, 96, 128 wide) or 1/65, 1/240, 1/740,
-// 1/1200, 1/2800 (two; largest error over 8192 pixels, nets drawn at random, a
-// texel that raises X so that little else is seen).  A 16-pixel group counts only
-// if each of its pixels has, for each channel, an output bias or one of its four
-// partial sums of at least E_c times 2^16 (no hidden matrix, or a layer under 32
-// wide), 2^14 (under 64), 2^13 (under 96), 2^12 (under 128) or 2^11, half of that
-// with two: what is lost in fact is then at most about 4e-7 of it, where binary32
-// sums are off by 3e-7 (rms) to 2e-6 of it.  Other groups are evaluated again by
-// the fp32 matrix instructions.  Nets of any common distribution pass by a factor
-// of 10 to 1000, whatever the scales of their levels, neurons and biases; tiles
-// with a texel 2^14 times larger than the rest, nets whose sums cancel and pixels
-// that no neuron is active at do not.
+// that do not all point one way, is 1/50 of it (no hidden matrix), 1/60, 1/130,
+// 1/500, 1/620, 1/1250, 1/2600 (one, 16, 32, 40, 64, 96, 128 wide) or 1/145,
+// 1/420, 1/560, 1/1500, 1/3300, 1/7300 (two; largest error over 8192 pixels, nets
+// drawn at random, a texel that raises X so that little else is seen).  A 16-pixel
+// group counts only if each of its pixels has, for each channel, an output bias or
+// one of its four partial sums of at least E_c times 2^15 (no hidden matrix, or a
+// layer under 40 wide), 2^13 (under 64), 2^12 (under 96), 2^11 (under 128) or
+// 2^10, half of that with two: what is lost in fact is then at most 3e-7 to 6e-7
+// of it, where binary32 sums are off by 3e-7 (rms) to 2e-6 of it.  Other groups
+// are evaluated again by the fp32 matrix instructions.  Nets of any common
+// distribution pass by a factor of 10 to 1000, whatever the scales of their
+// levels, neurons and biases; tiles with a texel 2^14 times larger than the rest,
+// nets whose sums cancel and pixels that no neuron is active at do not.
 //
 // Range.  A workgroup with a weight or bias of 2^24 or more or B_n of 2^90, a
 // tile with a level of 2^24 or more (NaN and infinities included), and one whose
@@ -206,8 +206,11 @@ __device__ __forceinline__ unsigned lower(unsigned h)
     return __builtin_bit_cast(unsigned, __builtin_bit_cast(f16x2, h) * f16x2{k, k});
 }
 
-// The parts of a pair of weights: h, l 2^kLow, third 2^kLow; lost: what the
-// first two leave of weights below 2^-14 (those above keep 23 bits), 2^kLow.
+// The parts of a pair of weights: h, l 2^kLow, third 2^kLow; lost: what is left
+// out of their products, for an activation of 1 and 2^kLow, of weights below
+// 2^-14 (of those above, it is as small against the product as elsewhere): what
+// the first two parts leave, and l against the activation's lower part, at most
+// 2^-11.
 struct WeightParts {
     unsigned h, l, third;
     float lost;
@@ -232,7 +235,8 @@ __device__ __forceinline__ WeightParts split_weights(float x0, float x1)
     const unsigned l = pack(r0, r1);
     const float t0 = rest(l, r0, false), t1 = rest(l, r1, true);
     return WeightParts{h, l, pack(t0, t1),
-                       (fabsf(x0) < 0x1p-14f ? fabsf(t0) : 0.0f) + (fabsf(x1) < 0x1p-14f ? fabsf(t1) : 0.0f)};
+                       (fabsf(x0) < 0x1p-14f ? __builtin_fmaf(fabsf(r0), 0x1p-11f, fabsf(t0)) : 0.0f) +
+                           (fabsf(x1) < 0x1p-14f ? __builtin_fmaf(fabsf(r1), 0x1p-11f, fabsf(t1)) : 0.0f)};
 }
 
 __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
@@ -695,9 +699,9 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
                 }
                 // a row's inputs off by err, their upper parts times 2^-kLow by
                 // 2^-25 against lower parts of 2^(kLow - 11) |w| (or 2^(kLow -
-                // 25)), its weights by `lost` 2^-kLow against 2^15 (1 + l / 4)
+                // 25)), its weights by `lost` 2^-kLow against 2^15 (1 + l / 8)
                 worst = fmaxf(worst, row_sum(__builtin_fmaf(l1, err + (float)(1 << kLow) * 0x1p-11f,
-                                                            lost * (0x1p40f * (1.0f + 0.25f * l) / (1 << kLow)))));
+                                                            lost * (0x1p40f * (1.0f + 0.125f * l) / (1 << kLow)))));
             }
             // (a bias in the operands, at most 2, loses up to 2^-37 against its
             // activation of at most 2^12, and up to 2^-12 against one below 2^-12)
@@ -727,7 +731,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
         const float level = fmaxf(fminf(bmax, one), 0x1p-60f);
         xfloor = 8.0f * level;
         rho = 0.5f * pow2_above(level);
-        steep = __builtin_amdgcn_readfirstlane(bmax > 4.0f * rho) != 0;
+        steep = __builtin_amdgcn_readfirstlane(bmax > 2.0f * rho) != 0;
         const float irho = pow2_inverse(rho);
 #pragma unroll
         for (int j = 0; j < BPW; ++j) {
@@ -772,7 +776,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
         }
         __syncthreads();
     }
-    // a channel's least acceptable partial sum: E_c times 2^16 to 2^10 (the
+    // a channel's least acceptable partial sum: E_c times 2^15 to 2^9 (the
     // header says why), by the narrowest hidden layer
     float thr[3];
     {
@@ -780,7 +784,7 @@ __global__ __launch_bounds__(kThreads) void k_mfma_f16x3(DecodeParams p, int blo
 #pragma unroll
         for (int l = 2; l <= NH + 1; ++l)
             n = min(n, p.widths[l]);
-        const float above = (NH == 0 || n < 32 ? 0x1p16f : n < 64 ? 0x1p14f : n < 96 ? 0x1p13f : n < 128 ? 0x1p12f : 0x1p11f) *
+        const float above = (NH == 0 || n < 40 ? 0x1p15f : n < 64 ? 0x1p13f : n < 96 ? 0x1p12f : n < 128 ? 0x1p11f : 0x1p10f) *
                             (NH == 2 ? 0.5f : 1.0f);
         const float err = max4(*reinterpret_cast<const f32x4 *>(&lds[LY::ERR + NH * kWaves])) * (above * 0x1p-25f);
 #pragma unroll
